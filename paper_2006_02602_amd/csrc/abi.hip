@@ -382,7 +382,7 @@ int step_impl(const cav_grid* grid, const cav_params* prm, const cav_halo* halo,
     auto go = [&](const char* name, auto&& launch) { return timed ? run(name, stream, launch) : launch(); };
     // the sweep of step n packs the i faces of step n+1's exchange when the
     // split allows (xfuse); that step's pack then moves the j and k faces
-    const bool xfuse = halo && xpack_fusable(hg);
+    const bool xfuse = halo && !g.point && xpack_fusable(hg);
     void* cur = q;
     void* nxt = q_tmp;
     hipError_t e;
@@ -406,7 +406,7 @@ int step_impl(const cav_grid* grid, const cav_params* prm, const cav_halo* halo,
     }
     if (norms) {
         const double ncell = (double)d.ni * d.nj * d.nk;
-        e = go("norm_finalize", [&] { return launch_norm_finalize(partials, g.nblocks, ncell, norms, stream); });
+        e = go("norm_finalize", [&] { return launch_norm_finalize(partials, g.npart, ncell, norms, stream); });
         if (e != hipSuccess) return hip_fail("norm finalize launch", e);
     }
     if (cur != q) {
@@ -503,7 +503,7 @@ int overlap_impl(const cav_grid* grid, const cav_params* prm, const HaloGeom& hg
     int rc;
     const Dims d = dims_of(grid);
     const Coef c = coef_of(grid, prm);
-    const SweepGeom gi = step_geom<Real>(d, device_slots());   // interior: the step sweep's tile
+    const SweepGeom gi = tile_geom<Real>(d, device_slots());   // interior: the step sweep's tile
     const SweepGeom g = sweep_geom(d, device_slots());          // exterior slabs: the 64 x 8 tiling
     SplitGeom sg;
     if ((rc = split_geom(grid, hg, gi, g, ws_bytes, &sg))) return rc;
@@ -660,7 +660,7 @@ int cavity_step_from(const cav_grid* grid, const cav_params* prm, const void* q_
         if (ws) {
             const double ncell = (double)d.ni * d.nj * d.nk;
             e = run("norm_finalize", stream,
-                    [&] { return launch_norm_finalize(partials, g.nblocks, ncell, norms, stream); });
+                    [&] { return launch_norm_finalize(partials, g.npart, ncell, norms, stream); });
             if (e != hipSuccess) return hip_fail("norm finalize launch", e);
         }
         return (int)CAV_OK;
@@ -674,8 +674,9 @@ int cavity_step_noalloc(const cav_grid* grid, const cav_params* prm, const cav_h
     int rc;
     HaloGeom hg;
     if ((rc = check_step(grid, prm, halo, q, q_tmp, halo_buf, halo_bytes, nsteps, &hg))) return rc;
-    const SweepGeom g = grid->dtype == CAV_F32 ? step_geom<float>(dims_of(grid), device_slots())
-                                               : step_geom<double>(dims_of(grid), device_slots());
+    // the limit holds for the marching tile's blocks, whichever kernel runs
+    const SweepGeom g = grid->dtype == CAV_F32 ? tile_geom<float>(dims_of(grid), device_slots())
+                                               : tile_geom<double>(dims_of(grid), device_slots());
     if (norms && g.nblocks > NOALLOC_MAX_BLOCKS)
         return fail(CAV_ESIZE,
                     "grid %d x %d x %d: its sweep runs %d blocks, whose norm partials exceed the static scratch "
@@ -998,9 +999,9 @@ int cavity_stream_copy(const cav_grid* grid, const void* q, void* q_tmp, hipStre
     const Dims d = dims_of(grid);
     hipError_t e = run("stream_copy", stream, [&] {
         return grid->dtype == CAV_F32
-                   ? launch_stream_copy<float>(d, step_geom<float>(d, device_slots()), cstate_of<float>(q, d),
+                   ? launch_stream_copy<float>(d, tile_geom<float>(d, device_slots()), cstate_of<float>(q, d),
                                                state_of<float>(q_tmp, d), stream)
-                   : launch_stream_copy<double>(d, step_geom<double>(d, device_slots()), cstate_of<double>(q, d),
+                   : launch_stream_copy<double>(d, tile_geom<double>(d, device_slots()), cstate_of<double>(q, d),
                                                 state_of<double>(q_tmp, d), stream);
     });
     return e == hipSuccess ? CAV_OK : hip_fail("stream copy launch", e);

@@ -261,7 +261,7 @@ __global__ __launch_bounds__(SW_TI * SW_TJ) void record_kernel(Dims d, Coef cd, 
     const CoefR<double> c = coef_as<double>(cd);
     const TileBox tb = tile_box(d, g.tiles_i, g.tiles_j, g.kc, xcd_block(blockIdx.x, g.nblocks));
     RecordEpiD<COMPACT> epi{{lam, rec, (long long)d.ni * d.nj * d.nk, rf, cx, -1}, d};
-    sweep_tile<double, true, OwnAll, RecordEpiD<COMPACT>, 2>(d, c, tb, OwnAll{}, q, epi, partials, L);
+    sweep_tile<double, true, OwnAll, RecordEpiD<COMPACT>>(d, c, tb, OwnAll{}, q, epi, partials, L);
 }
 
 // The record pass's per-block partials (the Ra term, the sum of lambda_p)

@@ -70,26 +70,22 @@ struct SweepGeom {
     int kc;                   // k planes per block
     int nkc;                  // k chunks
     int nblocks;              // tiles_i * tiles_j * nkc
+    bool point, point_norm;   // the step without / with norms runs one cell per thread
+    int npart;                // norm partials of the step with norms
 };
 // slots: blocks resident at once; ti x tj: the tile of the launch
 SweepGeom sweep_geom(const Dims& d, int slots, int ti = SW_TI, int tj = SW_TJ);
 // Tile of the single-cavity step sweep in FP32: 32 x 8 threads, four
-// wavefronts, so that three blocks stay resident per compute unit at that
+// wavefronts, so that four blocks stay resident per compute unit at that
 // kernel's register count (FP64 keeps SW_TI x SW_TJ, one block of eight).
 constexpr int F32_TI = 32, F32_TJ = 8;
-#ifndef CAV_F64_STEP_TJ
-#define CAV_F64_STEP_TJ 8
-#endif
-#ifndef CAV_F64_STEP_DEPTH
-#define CAV_F64_STEP_DEPTH 3
-#endif
-#ifndef CAV_F64_STEP_WAVES
-#define CAV_F64_STEP_WAVES 0
-#endif
-constexpr int F64_TI = 64, F64_TJ = CAV_F64_STEP_TJ;
-// Geometry of the step sweep for element type Real on `cus` compute units
-// (its tile, and the resident blocks per compute unit the occupancy query
-// reports).
+constexpr int F64_TI = 64, F64_TJ = 8;
+// Geometry of the marching step tile for element type Real on `cus` compute
+// units (the resident blocks per compute unit are what the occupancy query
+// reports), and of the unsplit step: that tile, or for a small grid the
+// one-cell-per-thread kernel.
+template <typename Real>
+SweepGeom tile_geom(const Dims& d, int cus);
 template <typename Real>
 SweepGeom step_geom(const Dims& d, int cus);
 

@@ -1,6 +1,6 @@
 // Per-cell stencil code shared by the forward sweep and its adjoint: the
 // coefficient struct, the stars of one cell, the residual of Eq. 1-3, the
-// wall ghost rules and the generic (slow) gather of one cell's stars.
+// wall ghost rules and the stars of one cell read from global memory.
 // Included by sweep.hip and adjoint.hip only; both are built with
 // -ffp-contract=off.
 #pragma once
@@ -142,107 +142,130 @@ __device__ __forceinline__ void cell_residual(const CoefR<Real>& c, const Star<R
 //   u, v, w:  g = -q(m_{g-1})                          (no-slip)
 //   T:        g = 2 T_wall - q(m_{g-1}) on the hot (x = 0) and cold (x = 1)
 //             walls, g = q(m_{g-1}) on the adiabatic walls.
-enum { SIDE_X_LO = 0, SIDE_X_HI = 1, SIDE_OTHER = 2 };
-constexpr int SLOT_UNUSED = 3;
+// The wall ghosts of one cell's stars along axis AX, by these rules from the
+// star's own values: m0 of a ghost is the cell itself or its neighbour
+// towards the wall, m1 the next one (the extents are >= 2).  x: the cell's
+// coordinate along the axis, n its extent; j, k: its hot-wall row.
+template <int AX, typename Real>
+__device__ __forceinline__ void star_ghosts_axis(int x, int n, Star<Real>& s, const CoefR<Real>& c, const Dims& d, int j,
+                                                 int k)
+{
+#define STAR_AX(nm, sfx) (AX == 0 ? s.nm##x##sfx : (AX == 1 ? s.nm##y##sfx : s.nm##z##sfx))
+    if (x == 0) {
+        STAR_AX(p, m) = Real(2) * s.p - STAR_AX(p, p);
+        STAR_AX(u, m) = -s.u;
+        STAR_AX(v, m) = -s.v;
+        STAR_AX(w, m) = -s.w;
+        STAR_AX(t, m) = AX == 0 ? Real(2) * hot_wall(c, d, j, k) - s.t : s.t;
+    }
+    if (x == n - 1) {
+        STAR_AX(p, p) = Real(2) * s.p - STAR_AX(p, m);
+        STAR_AX(u, p) = -s.u;
+        STAR_AX(v, p) = -s.v;
+        STAR_AX(w, p) = -s.w;
+        STAR_AX(t, p) = AX == 0 ? Real(2) * c.t_cold - s.t : s.t;
+    }
+    if (x <= 1) STAR_AX(p, m2) = Real(2) * STAR_AX(p, m) - s.p;
+    if (x >= n - 2) STAR_AX(p, p2) = Real(2) * STAR_AX(p, p) - s.p;
+#undef STAR_AX
+}
 
-// Where a thread reads one (i, j) column of every plane: the cell itself
-// (code 0), or the two mirror cells of a face ghost (code = g | side << 2),
-// or nothing (edge/corner column or beyond the ghosts: code 3).
-struct Slot {
-    int oa, ob, code;
+// A cell's place in the grid and the byte offsets, from element `base` of a
+// field, of it and of its neighbours one and two cells away per axis (its own
+// offset where that neighbour lies beyond a wall).  32-bit offsets from a
+// uniform base cost one register and no 64-bit arithmetic per load; the
+// caller picks base so that they fit.
+struct PointCell {
+    int i, j, k, base;
+    uint32_t o, xm, xp, xm2, xp2, ym, yp, ym2, yp2, zm, zp, zm2, zp2;
 };
 
-__device__ __forceinline__ Slot make_slot(const Dims& d, int i, int j)
+template <typename Real>
+__device__ __forceinline__ PointCell point_cell(const Dims& d, int i, int j, int k, int base)
 {
-    Slot s{0, 0, SLOT_UNUSED};
-    const bool ii = i >= 0 && i < d.ni, jj = j >= 0 && j < d.nj;
-    if (ii && jj) {
-        s.oa = cell_off(d, i, j, 0);
-        s.code = 0;
-    } else if (!ii && jj) {
-        const bool lo = i < 0;
-        const int g = lo ? -i : i - d.ni + 1;
-        if (g <= NG) {
-            s.oa = cell_off(d, lo ? 0 : d.ni - 1, j, 0);
-            s.ob = cell_off(d, lo ? 1 : d.ni - 2, j, 0);
-            s.code = g | ((lo ? SIDE_X_LO : SIDE_X_HI) << 2);
+    PointCell e;
+    e.i = i; e.j = j; e.k = k; e.base = base;
+    const uint32_t B = sizeof(Real), sy = d.sy * B, sz = d.sz * B;
+    e.o = (uint32_t)(cell_off(d, i, j, k) - base) * B;
+    e.xm = i > 0 ? e.o - B : e.o;         e.xm2 = i > 1 ? e.o - 2 * B : e.o;
+    e.xp = i < d.ni - 1 ? e.o + B : e.o;  e.xp2 = i < d.ni - 2 ? e.o + 2 * B : e.o;
+    e.ym = j > 0 ? e.o - sy : e.o;        e.ym2 = j > 1 ? e.o - 2 * sy : e.o;
+    e.yp = j < d.nj - 1 ? e.o + sy : e.o; e.yp2 = j < d.nj - 2 ? e.o + 2 * sy : e.o;
+    e.zm = k > 0 ? e.o - sz : e.o;        e.zm2 = k > 1 ? e.o - 2 * sz : e.o;
+    e.zp = k < d.nk - 1 ? e.o + sz : e.o; e.zp2 = k < d.nk - 2 ? e.o + 2 * sz : e.o;
+    return e;
+}
+
+// The centre cell of the rescale (Sec. 2).  Its star lies within two planes.
+template <typename Real>
+__device__ __forceinline__ PointCell centre_cell(const Dims& d)
+{
+    const int i = d.ni / 2, j = d.nj / 2, k = d.nk / 2;
+    return point_cell<Real>(d, i, j, k, cell_off(d, i, j, k) - 2 * d.sz);
+}
+
+// The value of the lane below (UP = false) or above in the wavefront; the
+// lane at its end keeps `end`.
+template <bool UP>
+__device__ __forceinline__ uint32_t lane_next(uint32_t v, uint32_t end)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)end, (int)v, UP ? 0x130 : 0x138, 0xf, 0xf, false);
+}
+template <bool UP>
+__device__ __forceinline__ float lane_next(float v, float end)
+{
+    return __builtin_bit_cast(float, lane_next<UP>(__builtin_bit_cast(uint32_t, v), __builtin_bit_cast(uint32_t, end)));
+}
+template <bool UP>
+__device__ __forceinline__ double lane_next(double v, double end)
+{
+    const uint64_t a = __builtin_bit_cast(uint64_t, v), b = __builtin_bit_cast(uint64_t, end);
+    const uint64_t lo = lane_next<UP>((uint32_t)a, (uint32_t)b), hi = lane_next<UP>((uint32_t)(a >> 32), (uint32_t)(b >> 32));
+    return __builtin_bit_cast(double, lo | hi << 32);
+}
+
+// The stars of one cell straight from global memory, all loads independent
+// of each other, then its wall ghosts.  ROW: the wavefront's lanes hold
+// 64 consecutive cells, so the x neighbours are the adjacent lanes' cells
+// (moved, not loaded: 29 loads instead of 41) and only the two end lanes load
+// theirs; every lane must be active.
+template <typename Real, bool ROW = false>
+__device__ __forceinline__ void point_star(const Dims& d, const CStateT<Real>& q, const CoefR<Real>& c,
+                                           const PointCell& e, Star<Real>& s)
+{
+    auto at = [&](int f, uint32_t off) __attribute__((always_inline)) {
+        return *reinterpret_cast<const Real*>(reinterpret_cast<const char*>(q.f[f] + e.base) + off);
+    };
+    Real end1[NF], end2 = Real(0);
+    if constexpr (ROW) {
+        const int lane = threadIdx.x & 63;
+#pragma unroll
+        for (int f = 0; f < NF; ++f) end1[f] = Real(0);
+        if (lane == 0 || lane == 63) {
+            end2 = at(FP, lane ? e.xp2 : e.xm2);
+#pragma unroll
+            for (int f = 0; f < NF; ++f) end1[f] = at(f, lane ? e.xp : e.xm);
         }
-    } else if (ii && !jj) {
-        const bool lo = j < 0;
-        const int g = lo ? -j : j - d.nj + 1;
-        if (g <= NG) {
-            s.oa = cell_off(d, i, lo ? 0 : d.nj - 1, 0);
-            s.ob = cell_off(d, i, lo ? 1 : d.nj - 2, 0);
-            s.code = g | (SIDE_OTHER << 2);
-        }
     }
-    return s;
-}
-
-// t_lo: the hot-wall temperature at this ghost's (j, k) (used on x = 0 only)
-template <typename Real>
-__device__ __forceinline__ Real ghost_value(int f, int code, Real a, Real b, const CoefR<Real>& c, Real t_lo)
-{
-    const int g = code & 3, side = code >> 2;
-    if (f == FP) {
-        const Real g1 = Real(2) * a - b;
-        return g == 1 ? g1 : Real(2) * g1 - a;
-    }
-    const Real m = g == 1 ? a : b;
-    if (f == FT) return side == SIDE_X_LO ? Real(2) * t_lo - m : (side == SIDE_X_HI ? Real(2) * c.t_cold - m : m);
-    return -m;
-}
-
-template <typename Real>
-__device__ __forceinline__ Real slot_load(const Real* G, const Slot& s, int kz, int f, const CoefR<Real>& c,
-                                          Real t_lo)
-{
-    Real v = Real(0);
-    if (s.code == 0)
-        v = G[s.oa + kz];
-    else if (s.code != SLOT_UNUSED)
-        v = ghost_value(f, s.code, G[s.oa + kz], G[s.ob + kz], c, t_lo);
-    return v;
-}
-
-// Any interior or face-ghost value, straight from global memory (used once
-// per block, for the stars of the centre cell).
-template <typename Real>
-__device__ __forceinline__ Real value_at(const Dims& d, const CStateT<Real>& q, const CoefR<Real>& c, int f, int i, int j,
-                                           int k)
-{
-    const Real* G = q.f[f];
-    if (k < 0 || k >= d.nk) {
-        const bool lo = k < 0;
-        const int g = lo ? -k : k - d.nk + 1;
-        const Real a = G[cell_off(d, i, j, lo ? 0 : d.nk - 1)];
-        const Real b = G[cell_off(d, i, j, lo ? 1 : d.nk - 2)];
-        return ghost_value(f, g | (SIDE_OTHER << 2), a, b, c, c.t_hot);
-    }
-    // the wall field is read only for an x = 0 ghost, whose row (j, k) is in range
-    const Real t_lo = (f == FT && i < 0 && j >= 0 && j < d.nj) ? hot_wall(c, d, j, k) : c.t_hot;
-    return slot_load(G, make_slot(d, i, j), k * d.sz, f, c, t_lo);
-}
-
-template <typename Real>
-__device__ __forceinline__ void gather_global(const Dims& d, const CStateT<Real>& q, const CoefR<Real>& c, int i, int j, int k,
-                                              Star<Real>& s)
-{
-    auto P = [&](int di, int dj, int dk) { return value_at(d, q, c, FP, i + di, j + dj, k + dk); };
-    s.p = P(0, 0, 0);
-    s.pxm = P(-1, 0, 0); s.pxp = P(1, 0, 0); s.pxm2 = P(-2, 0, 0); s.pxp2 = P(2, 0, 0);
-    s.pym = P(0, -1, 0); s.pyp = P(0, 1, 0); s.pym2 = P(0, -2, 0); s.pyp2 = P(0, 2, 0);
-    s.pzm = P(0, 0, -1); s.pzp = P(0, 0, 1); s.pzm2 = P(0, 0, -2); s.pzp2 = P(0, 0, 2);
-#define STAR7(F, nm)                                                                  \
-    {                                                                                 \
-        auto A = [&](int di, int dj, int dk) { return value_at(d, q, c, F, i + di, j + dj, k + dk); }; \
-        s.nm = A(0, 0, 0);                                                            \
-        s.nm##xm = A(-1, 0, 0); s.nm##xp = A(1, 0, 0);                                \
-        s.nm##ym = A(0, -1, 0); s.nm##yp = A(0, 1, 0);                                \
-        s.nm##zm = A(0, 0, -1); s.nm##zp = A(0, 0, 1);                                \
-    }
-    STAR7(FU, u) STAR7(FV, v) STAR7(FW, w) STAR7(FT, t)
-#undef STAR7
+    s.p = at(FP, e.o);
+    s.pym = at(FP, e.ym); s.pyp = at(FP, e.yp); s.pym2 = at(FP, e.ym2); s.pyp2 = at(FP, e.yp2);
+    s.pzm = at(FP, e.zm); s.pzp = at(FP, e.zp); s.pzm2 = at(FP, e.zm2); s.pzp2 = at(FP, e.zp2);
+#define POINT_STAR5(F, nm)                                \
+    s.nm = at(F, e.o);                                    \
+    s.nm##ym = at(F, e.ym); s.nm##yp = at(F, e.yp);       \
+    s.nm##zm = at(F, e.zm); s.nm##zp = at(F, e.zp);
+    POINT_STAR5(FU, u) POINT_STAR5(FV, v) POINT_STAR5(FW, w) POINT_STAR5(FT, t)
+#undef POINT_STAR5
+#define POINT_X(F, nm)                                                                                  \
+    s.nm##xm = ROW ? lane_next<false>(s.nm, end1[F]) : at(F, e.xm);                                     \
+    s.nm##xp = ROW ? lane_next<true>(s.nm, end1[F]) : at(F, e.xp);
+    POINT_X(FP, p) POINT_X(FU, u) POINT_X(FV, v) POINT_X(FW, w) POINT_X(FT, t)
+#undef POINT_X
+    s.pxm2 = ROW ? lane_next<false>(s.pxm, end2) : at(FP, e.xm2);
+    s.pxp2 = ROW ? lane_next<true>(s.pxp, end2) : at(FP, e.xp2);
+    star_ghosts_axis<0>(e.i, d.ni, s, c, d, e.j, e.k);
+    star_ghosts_axis<1>(e.j, d.nj, s, c, d, e.j, e.k);
+    star_ghosts_axis<2>(e.k, d.nk, s, c, d, e.j, e.k);
 }
 
 // Map hardware block ids (dispatched round-robin over the 8 XCDs) to tiles

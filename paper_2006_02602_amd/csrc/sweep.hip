@@ -21,17 +21,14 @@
 namespace cav {
 
 // Tile of the step sweep: FP64 64 x 8 (eight wavefronts; at its register
-// count one block per compute unit), FP32 32 x 8 (four wavefronts; three
-// resident blocks per compute unit, whose barriers interleave).
+// count, 199, one block per compute unit), FP32 32 x 8 (four wavefronts; 123
+// registers, four resident blocks per compute unit, whose barriers
+// interleave).
 template <typename Real>
 struct StepTile {
     static constexpr int TI = sizeof(Real) == 4 ? F32_TI : F64_TI;
     static constexpr int TJ = sizeof(Real) == 4 ? F32_TJ : F64_TJ;
     static constexpr int THREADS = TI * TJ;
-    // minimum waves per SIMD the compiler must fit (0: its own choice)
-    static constexpr int MINW = sizeof(Real) == 4 ? 0 : CAV_F64_STEP_WAVES;
-    // planes of loads in flight ahead of the computed plane
-    static constexpr int DEPTH = sizeof(Real) == 4 ? 3 : CAV_F64_STEP_DEPTH;
 };
 
 // The step's epilogue with the i-face part of the next exchange's pack
@@ -97,7 +94,7 @@ struct StepXPackEpi : StepEpi<Real> {
 // need no field loads (the kernel the uniform-wall problem runs).  XP: the
 // epilogue also packs the i faces of the new state into xbuf (geometry xh).
 template <typename Real, bool NORM, bool FIELD, bool XP>
-__global__ __launch_bounds__(StepTile<Real>::THREADS, StepTile<Real>::MINW) void sweep_kernel(
+__global__ __launch_bounds__(StepTile<Real>::THREADS) void sweep_kernel(
     Dims d, Coef cd, SweepGeom g, CStateT<Real> q, StateT<Real> qn, double* partials, XPackGeom xg, Real* xbuf)
 {
     constexpr int TI = StepTile<Real>::TI, TJ = StepTile<Real>::TJ;
@@ -113,12 +110,92 @@ __global__ __launch_bounds__(StepTile<Real>::THREADS, StepTile<Real>::MINW) void
         epi.buf = xbuf;
         const int tid = threadIdx.x + SW_TI * threadIdx.y;
         epi.init(d, tb.i0 + tid % TI);
-        sweep_tile<Real, NORM, OwnAll, StepXPackEpi<Real>, StepTile<Real>::DEPTH, TI, TJ>(d, c, tb, OwnAll{}, q, epi,
+        sweep_tile<Real, NORM, OwnAll, StepXPackEpi<Real>, TI, TJ>(d, c, tb, OwnAll{}, q, epi,
                                                                                          partials, L);
     } else {
         StepEpi<Real> epi{qn, Real(0)};
-        sweep_tile<Real, NORM, OwnAll, StepEpi<Real>, StepTile<Real>::DEPTH, TI, TJ>(d, c, tb, OwnAll{}, q, epi,
+        sweep_tile<Real, NORM, OwnAll, StepEpi<Real>, TI, TJ>(d, c, tb, OwnAll{}, q, epi,
                                                                                     partials, L);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// The step of a small grid: one cell per thread, its star read straight from
+// global memory (L2 and the memory-side cache hold the state), no k march.
+// A launch of the marching tile lasts ~9 us (FP64) however few planes its
+// blocks march: start-up of the queues and planes, then a chain of barriers.
+// Here the chain is one round of independent loads, one residual and the
+// stores.  Per step, without norms, marching tile -> this kernel: FP64 16^3
+// 9.2 -> 4.5 us, 48^3 9.6 -> 6.3, 96^3 24.7 -> 21.4; FP32 16^3 6.0 -> 3.5,
+// 64^3 7.3 -> 5.4, 160^3 45.7 -> 38.
+//
+// A block is CELLS cells, consecutive in (k, j, i) order whatever the extents
+// (no idle lanes at ragged ones), and one more wavefront that updates the
+// centre cell for the rescale while the others update theirs.  FP64 is bound
+// by the loads of its stars (41 of 512 bytes a wavefront): the x neighbours
+// are moved between lanes (29 loads; 96^3 24.0 -> 21.4 us), and 7 + 1
+// wavefronts make two blocks fill a compute unit at four wavefronts per SIMD
+// (114 registers).  FP32 is bound by its instructions and loads all 41 (moves:
+// 160^3 38 -> 40 us).  SMALL (FP64, fewer blocks of 448 cells than compute
+// units): 192 cells a block, 16^3 5.5 -> 4.5 us.  The norm pass writes a partial
+// per 512 (FP64) or 256 (FP32) cells, which the workspace always holds.
+template <typename Real, bool NORM, bool SMALL>
+struct PointSweep {
+    static constexpr bool F32 = sizeof(Real) == 4;
+    static constexpr int CELLS = NORM ? (F32 ? 256 : 512) : (SMALL ? 192 : 448);
+    static constexpr int THREADS = CELLS + 64;
+};
+
+template <typename Real, bool NORM, bool SMALL>
+__global__ __launch_bounds__((PointSweep<Real, NORM, SMALL>::THREADS)) void point_sweep_kernel(
+    Dims d, Coef cd, CStateT<Real> q, StateT<Real> qn, double* partials)
+{
+    constexpr int CELLS = PointSweep<Real, NORM, SMALL>::CELLS;
+    __shared__ Real pc;
+    __shared__ double red[NORM ? CELLS / 64 : 1][NF];
+    const CoefR<Real> c = coef_as<Real>(cd);
+    const int blk = xcd_block(blockIdx.x, gridDim.x), tid = threadIdx.x;
+    const int n = d.ni * d.nj * d.nk;
+    // the last wavefront's cells: 64 consecutive ones with the centre among them
+    const bool extra = tid >= CELLS;
+    const int mc = d.ni / 2 + d.ni * (d.nj / 2 + d.nj * (d.nk / 2));
+    const int m = extra ? max(0, min(mc - 32, n - 64)) + tid - CELLS : blk * CELLS + tid;
+    const bool in = !extra && m < n;
+    const int mm = min(m, n - 1);
+    const int r = mm / d.ni;
+    const int i = mm - r * d.ni, k = r / d.nj, j = r - k * d.nj;
+    const PointCell e = point_cell<Real>(d, i, j, k, 0);
+    Star<Real> s;
+    point_star<Real, !PointSweep<Real, NORM, SMALL>::F32>(d, q, c, e, s);
+    Real R[NF], dt;
+    cell_residual(c, s, R, dt);
+    if (extra && m == mc) pc = fma(dt, R[FP], s.p);
+    __syncthreads();
+    auto put = [&](int f, Real v) __attribute__((always_inline)) {
+        *reinterpret_cast<Real*>(reinterpret_cast<char*>(qn.f[f]) + e.o) = v;
+    };
+    if (in) {
+        put(FP, fma(dt, R[FP], s.p) - pc);
+        put(FU, fma(dt, R[FU], s.u));
+        put(FV, fma(dt, R[FV], s.v));
+        put(FW, fma(dt, R[FW], s.w));
+        put(FT, fma(dt, R[FT], s.t));
+    }
+    if (NORM) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            double v = in ? (double)R[f] * (double)R[f] : 0.0;
+#pragma unroll
+            for (int x = 32; x >= 1; x >>= 1) v += __shfl_xor(v, x, 64);
+            if ((tid & 63) == 0 && !extra) red[tid >> 6][f] = v;
+        }
+        __syncthreads();
+        if (tid < NF) {
+            double t = 0.0;
+#pragma unroll
+            for (int w = 0; w < CELLS / 64; ++w) t += red[w][tid];
+            partials[(size_t)blk * NF + tid] = t;
+        }
     }
 }
 
@@ -131,7 +208,7 @@ template <typename Real>
 __global__ __launch_bounds__(StepTile<Real>::THREADS) void stream_copy_kernel(Dims d, SweepGeom g, CStateT<Real> q,
                                                                               StateT<Real> qn)
 {
-    constexpr int TI = StepTile<Real>::TI, TJ = StepTile<Real>::TJ, DEPTH = StepTile<Real>::DEPTH;
+    constexpr int TI = StepTile<Real>::TI, TJ = StepTile<Real>::TJ, DEPTH = 2;   // the sweep's look-ahead
     const TileBox tb = tile_box<TI, TJ>(d, g.tiles_i, g.tiles_j, g.kc, xcd_block(blockIdx.x, g.nblocks));
     const int tid = threadIdx.x + SW_TI * threadIdx.y;
     const int i = tb.i0 + tid % TI, j = tb.j0 + tid / TI;
@@ -214,11 +291,13 @@ SweepGeom sweep_geom(const Dims& d, int slots, int ti, int tj)
     g.kc = (d.nk + best - 1) / best;
     g.nkc = (d.nk + g.kc - 1) / g.kc;
     g.nblocks = tiles * g.nkc;
+    g.point = g.point_norm = false;
+    g.npart = g.nblocks;
     return g;
 }
 
 template <typename Real>
-SweepGeom step_geom(const Dims& d, int cus)
+SweepGeom tile_geom(const Dims& d, int cus)
 {
     // resident blocks per compute unit of the step kernel (registers and LDS
     // decide it); the same for every launch on this device
@@ -233,6 +312,33 @@ SweepGeom step_geom(const Dims& d, int cus)
     }
     return sweep_geom(d, cus * per_cu, StepTile<Real>::TI, StepTile<Real>::TJ);
 }
+template SweepGeom tile_geom<double>(const Dims&, int);
+template SweepGeom tile_geom<float>(const Dims&, int);
+
+// The tile, or one cell per thread where that is faster.  FP32: while both
+// states stay in the 256 MB memory-side cache (160^3, 164 MB: 38 against 46
+// us; 176^3, 218 MB: 59-66 against 63 us).  FP64: by both kernels' measured
+// cost in us: the tile 2.0 a plane of its blocks, with 2.2 planes of start-up
+// (80^3 20, 96^3 25, 128^3 42, 161x97x130 47), the other 4 + 21 per million
+// cells (15, 21, 46, 46); they cross between 96^3 and 128^3, later where the
+// extents leave lanes of the tile idle.  (A grid of 4.2 million cells has at
+// most 48 (FP64) or 96 (FP32) padded elements a cell, so that kernel's byte
+// offsets fit in 32 bits.)  With norms only up to 150 thousand cells: each
+// wavefront's five butterflies cost as much as its residual (161x97x130: 190
+// us against the tile's 125 for a step, its norms and the copy back).
+template <typename Real>
+SweepGeom step_geom(const Dims& d, int cus)
+{
+    SweepGeom g = tile_geom<Real>(d, cus);
+    const long long n = (long long)d.ni * d.nj * d.nk;
+    constexpr int CELLS = PointSweep<Real, true, false>::CELLS;
+    const int rounds = (g.nblocks + cus - 1) / cus;
+    g.point = sizeof(Real) == 4 ? n <= 4200000
+                                : n <= 4200000 && 4.0 + 21e-6 * (double)n < 1.0 + 2.0 * rounds * (g.kc + 2.2);
+    g.point_norm = g.point && n <= 150000;
+    if (g.point_norm) g.npart = (int)((n + CELLS - 1) / CELLS);
+    return g;
+}
 template SweepGeom step_geom<double>(const Dims&, int);
 template SweepGeom step_geom<float>(const Dims&, int);
 
@@ -245,6 +351,20 @@ hipError_t launch_sweep(const Dims& d, const Coef& c, const SweepGeom& g, CState
     dim3 block(SW_TI, StepTile<Real>::THREADS / SW_TI), grid(g.nblocks);
     XPackGeom xg{};
     const bool xp = xh && xbuf && !with_norm;
+    if (with_norm ? g.point_norm : g.point) {
+        const int n = d.ni * d.nj * d.nk;
+        const bool small = sizeof(Real) == 8 && n <= 448 * 128;
+#define POINT_LAUNCH(NRM, SM)                                                                              \
+    do {                                                                                                   \
+        using P = PointSweep<Real, NRM, SM>;                                                               \
+        point_sweep_kernel<Real, NRM, SM><<<(n + P::CELLS - 1) / P::CELLS, P::THREADS, 0, s>>>(d, c, q, qn, partials); \
+    } while (0)
+        if (with_norm) POINT_LAUNCH(true, false);
+        else if (small) POINT_LAUNCH(false, sizeof(Real) == 8);
+        else POINT_LAUNCH(false, false);
+#undef POINT_LAUNCH
+        return hipGetLastError();
+    }
     if (xp) {
         xg.ex = xh->e[0];
         xg.pi = xh->P[0];
@@ -339,7 +459,7 @@ __global__ __launch_bounds__(StepTile<Real>::THREADS) void interior_kernel(Dims 
     if constexpr (!FIELD) c.t_hot_field = nullptr;
     const TileBox tb = tile_box<TI, TJ>(d, g.tiles_i, g.tiles_j, g.kc, xcd_block(blockIdx.x, g.nblocks));
     StepEpi<Real> epi{qn, Real(0)};
-    sweep_tile<Real, NORM, OwnInterior, StepEpi<Real>, StepTile<Real>::DEPTH, TI, TJ>(d, c, tb, OwnInterior{sg}, q,
+    sweep_tile<Real, NORM, OwnInterior, StepEpi<Real>, TI, TJ>(d, c, tb, OwnInterior{sg}, q,
                                                                                      epi, partials, L);
 }
 
@@ -395,7 +515,7 @@ __global__ __launch_bounds__(SW_TI * SW_TJ) void exterior_kernel(Dims d, Coef cd
     tb.pidx = pidx0 + b;
     StepEpi<Real> epi{qn, Real(0)};
     if (axis == 0)          // 2m <= 8 owned columns: a narrow tile wastes fewer lanes
-        sweep_tile<Real, NORM, OwnSlab, StepEpi<Real>, 3, XS_TI, XS_TJ>(d, c, tb, OwnSlab{sg, axis, cut}, q, epi,
+        sweep_tile<Real, NORM, OwnSlab, StepEpi<Real>, XS_TI, XS_TJ>(d, c, tb, OwnSlab{sg, axis, cut}, q, epi,
                                                                       partials, L.x);
     else
         sweep_tile<Real, NORM>(d, c, tb, OwnSlab{sg, axis, cut}, q, epi, partials, L.yz);
@@ -456,8 +576,6 @@ struct BatchTiles {
     static constexpr int THREADS = batch_threads(F32);
     static constexpr int WTI = batch_wide_ti(F32), WTJ = batch_tj(F32, WTI);
     static constexpr int NTI = batch_narrow_ti(F32), NTJ = batch_tj(F32, NTI);
-    // prefetch depth: the FP64 kernel would spill a third register set
-    static constexpr int DEPTH = F32 ? 3 : 2;
     // waves per SIMD the one-shape FP32 kernels must fit (three 256-thread
     // blocks per CU, as the FP32 step sweep; 0: the compiler's choice)
     static constexpr int MINW1 = F32 ? 3 : 0;
@@ -511,11 +629,11 @@ __global__ __launch_bounds__(BatchTiles<Real>::THREADS, SHAPES == 3 ? 0 : BatchT
         StepEpi<Real> epi{qn, Real(0)};
         if (SHAPES == 2 || (SHAPES == 3 && cv.ti == BT::NTI)) {
             const TileBox tb = tile_box<BT::NTI, BT::NTJ>(d, cv.tiles_i, cv.tiles_j, cv.kc, w.tile);
-            sweep_tile<Real, NORM, OwnAll, StepEpi<Real>, BT::DEPTH, BT::NTI, BT::NTJ>(
+            sweep_tile<Real, NORM, OwnAll, StepEpi<Real>, BT::NTI, BT::NTJ>(
                 d, c, tb, OwnAll{}, qs, epi, cv.ws + WS_HEAD_DOUBLES, L.narrow);
         } else {
             const TileBox tb = tile_box<BT::WTI, BT::WTJ>(d, cv.tiles_i, cv.tiles_j, cv.kc, w.tile);
-            sweep_tile<Real, NORM, OwnAll, StepEpi<Real>, BT::DEPTH, BT::WTI, BT::WTJ>(
+            sweep_tile<Real, NORM, OwnAll, StepEpi<Real>, BT::WTI, BT::WTJ>(
                 d, c, tb, OwnAll{}, qs, epi, cv.ws + WS_HEAD_DOUBLES, L.wide);
         }
         __syncthreads();                  // LDS is reused by the next item
@@ -543,27 +661,42 @@ template hipError_t launch_batch<double>(const BatchCav*, const int*, const Batc
 template hipError_t launch_batch<float>(const BatchCav*, const int*, const BatchItem*, int, bool, int, int,
                                         hipStream_t);
 
-// Residual norms of every member: one block per member, the same
-// fixed-order reduction as the single-cavity finalize.
-__global__ __launch_bounds__(256) void batch_norm_kernel(const BatchCav* __restrict__ cavs)
+// Residual norms from per-block partials: fixed-order sums (each thread its
+// strided blocks in order, all fields of a block at once so that its loads
+// are independent; a butterfly within the wavefront; the wavefronts in
+// order), RMS over ncell.  Run by one block of T threads.  One field after the
+// other, with one load in flight per thread, 4000 partials took ~90 us.
+template <int T>
+__device__ __forceinline__ void finalize_norms(const double* __restrict__ part, int nb, double ncell,
+                                               double* __restrict__ out)
 {
-    __shared__ double red[NF][256];
-    const BatchCav& cv = cavs[blockIdx.x];
-    const double* part = cv.ws + WS_HEAD_DOUBLES;
+    __shared__ double red[T / 64][NF];
     const int t = threadIdx.x;
+    double s[NF] = {0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+    for (int b = t; b < nb; b += T)
+#pragma unroll
+        for (int f = 0; f < NF; ++f) s[f] += part[(size_t)b * NF + f];
+#pragma unroll
     for (int f = 0; f < NF; ++f) {
-        double s = 0.0;
-        for (int b = t; b < cv.ntiles; b += 256) s += part[(size_t)b * NF + f];
-        red[f][t] = s;
+#pragma unroll
+        for (int m = 32; m >= 1; m >>= 1) s[f] += __shfl_xor(s[f], m, 64);
+        if ((t & 63) == 0) red[t >> 6][f] = s[f];
     }
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w)
-            for (int f = 0; f < NF; ++f) red[f][t] += red[f][t + w];
-        __syncthreads();
+    if (t < NF) {
+        double v = 0.0;
+#pragma unroll
+        for (int w = 0; w < T / 64; ++w) v += red[w][t];
+        out[t] = sqrt(v / ncell);
     }
-    const double ncell = (double)cv.d.ni * cv.d.nj * cv.d.nk;
-    if (t < NF) cv.ws[t] = sqrt(red[t][0] / ncell);
+}
+
+// Residual norms of every member of a batch: one block per member.
+__global__ __launch_bounds__(256) void batch_norm_kernel(const BatchCav* __restrict__ cavs)
+{
+    const BatchCav& cv = cavs[blockIdx.x];
+    finalize_norms<256>(cv.ws + WS_HEAD_DOUBLES, cv.ntiles, (double)cv.d.ni * cv.d.nj * cv.d.nk, cv.ws);
 }
 
 hipError_t launch_batch_norms(const BatchCav* cavs, int members, hipStream_t s)
@@ -738,31 +871,16 @@ template hipError_t launch_nusselt<double>(const Dims&, const Bcs&, CStateT<doub
 template hipError_t launch_nusselt<float>(const Dims&, const Bcs&, CStateT<float>, double*, hipStream_t);
 
 // ---------------------------------------------------------------------------
-// Residual norms: fixed-order sum of the per-block partials (strided
-// per-thread sums, then a fixed tree), RMS over the interior.
-__global__ __launch_bounds__(256) void norm_finalize_kernel(const double* part, int nb, double ncell,
-                                                            double* out)
+// Residual norms of one cavity.
+__global__ __launch_bounds__(1024) void norm_finalize_kernel(const double* part, int nb, double ncell, double* out)
 {
-    __shared__ double red[NF][256];
-    const int t = threadIdx.x;
-    for (int f = 0; f < NF; ++f) {
-        double s = 0.0;
-        for (int b = t; b < nb; b += 256) s += part[(size_t)b * NF + f];
-        red[f][t] = s;
-    }
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w)
-            for (int f = 0; f < NF; ++f) red[f][t] += red[f][t + w];
-        __syncthreads();
-    }
-    if (t < NF) out[t] = sqrt(red[t][0] / ncell);
+    finalize_norms<1024>(part, nb, ncell, out);
 }
 
 hipError_t launch_norm_finalize(const double* partials, int nblocks, double ncell, double* out,
                                 hipStream_t s)
 {
-    norm_finalize_kernel<<<1, 256, 0, s>>>(partials, nblocks, ncell, out);
+    norm_finalize_kernel<<<1, 1024, 0, s>>>(partials, nblocks, ncell, out);
     return hipGetLastError();
 }
 

@@ -16,9 +16,9 @@ namespace cav {
 // the k neighbours come from per-thread register queues (p: k-2..k+2,
 // others k-1..k+1).  The LDS planes are double-buffered: plane k+1 is
 // written into one buffer while plane k is computed from the other, so each
-// plane costs one barrier; global loads run two or three planes ahead.  Wall ghosts
-// are derived from interior cells (in LDS for the i/j walls, by recurrences
-// on the queues for the k walls); no ghost cell is read from HBM.
+// plane costs one barrier; global loads run two planes ahead.  Wall ghosts
+// are derived from interior cells (in each cell's star for the i/j walls, by
+// recurrences on the queues for the k walls); no ghost cell is read from HBM.
 // LDS of one sweep block of TI x TJ threads: two planes of p (halo 2) and
 // of u, v, w, T (halo 1), and one norm slot per wavefront.
 template <typename Real, int TI_ = SW_TI, int TJ_ = SW_TJ>
@@ -46,7 +46,7 @@ struct StepEpi {
     __device__ __forceinline__ void prepare(const Dims& d, const CStateT<Real>& q, const CoefR<Real>& c)
     {
         Star<Real> s;
-        gather_global(d, q, c, d.ni / 2, d.nj / 2, d.nk / 2, s);
+        point_star(d, q, c, centre_cell<Real>(d), s);
         Real R[NF], dt;
         cell_residual(c, s, R, dt);
         pc_new = fma(dt, R[FP], s.p);
@@ -101,7 +101,7 @@ struct OwnAll {
 // TI * row works on column (i0 + lane, j0 + row); TI >= 16 and TJ >= 4 (the
 // halo roles below need 12 threads per row; 4-row tiles give each thread
 // two of the eight u v w T halo rows).
-template <typename Real, bool NORM, typename Own, typename Epi, int DEPTH = 3, int TI = SW_TI, int TJ = SW_TJ>
+template <typename Real, bool NORM, typename Own, typename Epi, int TI = SW_TI, int TJ = SW_TJ>
 __device__ __forceinline__ void sweep_tile(const Dims& d, const CoefR<Real>& c, const TileBox& tb, const Own& own,
                                            const CStateT<Real>& q, Epi& epi, double* partials,
                                            SweepLds<Real, TI, TJ>& L)
@@ -128,9 +128,9 @@ __device__ __forceinline__ void sweep_tile(const Dims& d, const CoefR<Real>& c, 
 
 
     // ---- what this thread loads (fixed for the whole march) ----
-    // Only interior cells are loaded.  LDS cells that hold wall ghosts are
-    // filled from interior LDS cells (fix_ghosts), the k neighbours beyond
-    // the z walls by recurrences on the register queues.
+    // Only interior cells are loaded.  LDS cells beyond a wall hold zeros and
+    // are read only into star values that star_ghosts_axis then replaces; the
+    // k neighbours beyond the z walls come by recurrences on the queues.
     auto interior = [&](int ii, int jj) { return ii >= 0 && ii < d.ni && jj >= 0 && jj < d.nj; };
     // p rows j0-2, j0-1, j0+TJ, j0+TJ+1: waves 0..3, one row each
     const bool has_prow = row < 4;
@@ -183,43 +183,8 @@ __device__ __forceinline__ void sweep_tile(const Dims& d, const CoefR<Real>& c, 
     const Real* const COLg = q.f[col_f];
     const int Z = d.sz;
 
-    // tiles whose LDS planes reach past a wall fix their ghost cells
-    const bool bnd = i0 == 0 || j0 == 0 || i0 + TI + 2 > d.ni || j0 + TJ + 2 > d.nj;
-    auto fix_ghosts = [&](Real* fP, Real* fU, int k) __attribute__((always_inline)) {
-        auto cell = [&](int f, int ci, int cj) -> Real& {
-            return f == FP ? fP[(cj - j0 + 2) * PW + (ci - i0 + 2)]
-                           : fU[(f - FU) * UPL + (cj - j0 + 1) * UW + (ci - i0 + 1)];
-        };
-        // y walls: column i0 + lane, fields row, row + TJ, ...
-        for (int f = row; f < NF && i < d.ni; f += TJ) {
-            const int reach = f == FP ? 2 : 1;
-            if (j0 == 0) {
-                const Real a = cell(f, i, 0), b = cell(f, i, 1);
-                for (int gg = 1; gg <= reach; ++gg) cell(f, i, -gg) = ghost_value(f, gg | (SIDE_OTHER << 2), a, b, c, c.t_hot);
-            }
-            if (j0 + TJ + reach > d.nj) {
-                const Real a = cell(f, i, d.nj - 1), b = cell(f, i, d.nj - 2);
-                for (int gg = 1; gg <= reach; ++gg)
-                    if (d.nj - 1 + gg < j0 + TJ + reach)
-                        cell(f, i, d.nj - 1 + gg) = ghost_value(f, gg | (SIDE_OTHER << 2), a, b, c, c.t_hot);
-            }
-        }
-        // x walls: row j0 + row, field `lane`
-        if (lane < NF && j < d.nj) {
-            const int f = lane, reach = f == FP ? 2 : 1;
-            if (i0 == 0) {
-                const Real a = cell(f, 0, j), b = cell(f, 1, j);
-                const Real tlo = hot_wall(c, d, j, k);
-                for (int gg = 1; gg <= reach; ++gg) cell(f, -gg, j) = ghost_value(f, gg | (SIDE_X_LO << 2), a, b, c, tlo);
-            }
-            if (i0 + TI + reach > d.ni) {
-                const Real a = cell(f, d.ni - 1, j), b = cell(f, d.ni - 2, j);
-                for (int gg = 1; gg <= reach; ++gg)
-                    if (d.ni - 1 + gg < i0 + TI + reach)
-                        cell(f, d.ni - 1 + gg, j) = ghost_value(f, gg | (SIDE_X_HI << 2), a, b, c, c.t_hot);
-            }
-        }
-    };
+    // tiles whose stars reach past an i or j wall (block-uniform)
+    const bool bnd_i = i0 == 0 || i0 + TI + 2 > d.ni, bnd_j = j0 == 0 || j0 + TJ + 2 > d.nj;
 
     // ---- register queues ----
     Real p0, p1, p2, p3;                                 // p at k-2, k-1, k, k+1
@@ -261,10 +226,9 @@ __device__ __forceinline__ void sweep_tile(const Dims& d, const CoefR<Real>& c, 
         if (has_urow[r]) sU[urow_dst[r]] = ld_urow[r] ? URg[r][off_urow[r] + k0 * Z] : Real(0);
     if (has_col) (col_f == FP ? sP : sU)[col_lds] = ld_col ? COLg[off_col + k0 * Z] : Real(0);
 
-    // Loads run DEPTH planes ahead: what the iteration for plane k needs
-    // from memory (queue heads p(k+2), uvwT(k+1), halo strips of plane k+1)
-    // is issued while plane k-DEPTH is computed; DEPTH register sets rotate
-    // (3 for the step kernels; 2 where the epilogue needs the registers).
+    // Loads run two planes ahead: what the iteration for plane k needs from
+    // memory (queue heads p(k+2), uvwT(k+1), halo strips of plane k+1) is
+    // issued while plane k-2 is computed; two register sets alternate.
     struct InFlight {
         Real p, u, v, w, t, prow, urow[UR], col;
     };
@@ -286,12 +250,9 @@ __device__ __forceinline__ void sweep_tile(const Dims& d, const CoefR<Real>& c, 
             if (ld_col) F.col = COLg[off_col + (k + 1) * Z];
         }
     };
-    static_assert(DEPTH == 2 || DEPTH == 3, "prefetch depth is 2 or 3 planes");
-    InFlight X{}, Y{}, Zs{};
+    InFlight X{}, Y{};
     issue(X, k0);
     if (k0 + 1 < k1) issue(Y, k0 + 1);
-    if constexpr (DEPTH == 3)
-        if (k0 + 2 < k1) issue(Zs, k0 + 2);
     // the epilogue's per-block setup (for the step: the centre cell's new
     // pressure, a star gathered from L2) overlaps the loads in flight
     epi.prepare(d, q, c);
@@ -321,14 +282,10 @@ __device__ __forceinline__ void sweep_tile(const Dims& d, const CoefR<Real>& c, 
                 if (has_urow[r]) nU[urow_dst[r]] = F.urow[r];
             if (has_col) (col_f == FP ? nP : nU)[col_lds] = F.col;
         }
-        if (k + DEPTH < k1) issue(F, k + DEPTH);
+        if (k + 2 < k1) issue(F, k + 2);
 
         Real* const cP = sP + buf * PPL;
         Real* const cU = sU + buf * 4 * UPL;
-        if (bnd) {
-            fix_ghosts(cP, cU, k);
-            __syncthreads();
-        }
         if (active && own(i, j, k)) {
             Star<Real> s;
             s.p = p2;
@@ -344,6 +301,8 @@ __device__ __forceinline__ void sweep_tile(const Dims& d, const CoefR<Real>& c, 
             STAR_LDS(w, 2, w1, w0, w2)
             STAR_LDS(t, 3, t1, t0, t2)
 #undef STAR_LDS
+            if (bnd_i && __any(i < 2 || i >= d.ni - 2)) star_ghosts_axis<0>(i, d.ni, s, c, d, j, k);
+            if (bnd_j && __any(j < 2 || j >= d.nj - 2)) star_ghosts_axis<1>(j, d.nj, s, c, d, j, k);
             Real R[NF], dt;
             cell_residual(c, s, R, dt);
             epi.cell(c, s, R, dt, off_c + k * Z, i, j, k, acc);
@@ -354,11 +313,9 @@ __device__ __forceinline__ void sweep_tile(const Dims& d, const CoefR<Real>& c, 
         u0 = u1; u1 = u2; v0 = v1; v1 = v2; w0 = w1; w1 = w2; t0 = t1; t1 = t2;
     };
 
-    for (int k = k0; k < k1; k += DEPTH) {
+    for (int k = k0; k < k1; k += 2) {
         plane(X, k);
         if (k + 1 < k1) plane(Y, k + 1);
-        if constexpr (DEPTH == 3)
-            if (k + 2 < k1) plane(Zs, k + 2);
     }
 
     if (NORM) {
