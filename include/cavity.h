@@ -296,14 +296,14 @@ int cavity_nusselt_adjoint(const cav_grid* grid, const cav_params* prm, void* la
 /* One reverse step: given lam_in = dJ/dq^{n+1} (device, state layout,
  * interior cells read) and q_n (device, the state the forward step started
  * from, interior cells read), writes lam_out = dJ/dq^n on the interior cells
- * (its ghost cells are used as scratch and left unspecified) and ADDS this
+ * (its ghost cells are left unspecified) and ADDS this
  * step's terms into dj_dthot (device, nj*nk doubles, j fastest) and dj_dra
  * (device, 1 double); either may be NULL to skip it.  lam_out must not
  * overlap lam_in (the gather reads lam_in at every cell's neighbours while
  * it writes lam_out) or q_n; CAV_EINVAL when it equals either.  ws: device, >=
- * cavity_adjoint_workspace_bytes.  Two launches on `stream` (the record
- * pass; the gather, which also forms the rescale sum and the Ra sum), no
- * allocation, no synchronisation.  CAV_EINVAL for a CAV_F32 grid. */
+ * cavity_adjoint_workspace_bytes.  Two launches on `stream` (the pass; the
+ * transpose of the rescale with the Ra sum), no allocation, no
+ * synchronisation.  CAV_EINVAL for a CAV_F32 grid. */
 int cavity_adjoint_step(const cav_grid* grid, const cav_params* prm,
                         const void* q_n, const void* lam_in, void* lam_out,
                         void* ws, size_t ws_bytes, double* dj_dthot,

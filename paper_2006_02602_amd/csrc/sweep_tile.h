@@ -1,6 +1,6 @@
-// The k-marching tile of the sweep, shared by the pseudo-time step
-// (sweep.hip) and the record pass of the discrete adjoint (adjoint.hip).
-// Included by those two files only; both are built with -ffp-contract=off.
+// The k-marching tile of the sweep (sweep.hip: the step, the batched form and
+// the interior/exterior split); its tile boxes serve the adjoint's tile too.
+// Built with -ffp-contract=off.
 #pragma once
 
 #include "cavity_internal.h"
