@@ -210,7 +210,8 @@ __device__ __forceinline__ void add_wall(GatherAcc& a, const RevCoef& c, int x, 
         a.Lw -= t.Lw;
         if (AX == 0) {
             a.Lt -= t.Lt;
-            if (DIR < 0 && dth) *dth += 2.0 * t.Lt;
+            // the row's only writer in this launch; an atomic so that nothing waits for the old value
+            if (DIR < 0 && dth) unsafeAtomicAdd(dth, 2.0 * t.Lt);
         } else {
             a.Lt += t.Lt;
         }
@@ -220,17 +221,16 @@ __device__ __forceinline__ void add_wall(GatherAcc& a, const RevCoef& c, int x, 
 }
 
 // The wall ghosts of one axis of a cell's stars (star_ghosts_axis for values
-// held per axis).
+// held per axis).  wall: the hot-wall temperature of the cell's row.
 template <int AX>
-__device__ __forceinline__ void axis_ghosts(const RevCoef& c, const Dims& d, int x, int n, int j, int k,
-                                            const double f0[NF - 1], double p0, double fm[NF - 1], double fp[NF - 1],
+__device__ __forceinline__ void axis_ghosts(const RevCoef& c, int x, int n, double wall, const double f0[NF - 1], double p0, double fm[NF - 1], double fp[NF - 1],
                                             double& pm, double& pp, double& pm2, double& pp2)
 {
     if (x == 0) {
         pm = 2.0 * p0 - pp;
 #pragma unroll
         for (int f = 0; f < 3; ++f) fm[f] = -f0[f];
-        fm[3] = AX == 0 ? 2.0 * hot_wall(c, d, j, k) - f0[3] : f0[3];
+        fm[3] = AX == 0 ? 2.0 * wall - f0[3] : f0[3];
     }
     if (x == n - 1) {
         pp = 2.0 * p0 - pm;
@@ -245,6 +245,13 @@ __device__ __forceinline__ void axis_ghosts(const RevCoef& c, const Dims& d, int
 // Keeps the compiler from moving work across a phase of the tile's plane:
 // left alone it issues every LDS read of a plane first and spills.
 #define PHASE() __builtin_amdgcn_sched_barrier(0)
+
+// A copy made here, in a register of its own.
+__device__ __forceinline__ double moved(double x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
+}
 
 // The value at 32-bit byte offset off from a uniform base.
 __device__ __forceinline__ double ldo(const double* base, uint32_t off)
@@ -261,10 +268,12 @@ __device__ __forceinline__ double ldo(const double* base, uint32_t off)
 // its plane is two ahead.  So every value is read from memory once per tile
 // plus the halo, and nothing is stored but lambda: 120 B per cell at least,
 // where a pass that stored the centre terms and one that gathered with them
-// moved 259 (256^3: 515 + 595 us in two passes, 660 in one).  160 KB of LDS
-// (one block per CU) and 235 VGPRs: the z neighbours' dt and Bp and the
+// moved 259 (256^3: 515 + 595 us in two passes, 535 in one).  160 KB of LDS
+// (one block per CU) and 236 VGPRs: the z neighbours' dt and Bp and the
 // in-plane X stay in LDS for their three planes rather than in registers.
-// Two eight-wave rounds of ~600 VALU instructions a plane bound it, not HBM.
+// Its loads run a plane ahead without conditions (with them every plane began
+// by waiting for all loads in flight: 660 us); what is left is the ~600 VALU
+// and ~75 LDS instructions a wavefront issues per plane, two to a SIMD.
 template <int TJ>
 struct ReverseTile {
     static constexpr int THREADS = 64 * TJ;
@@ -330,19 +339,20 @@ __global__ __launch_bounds__(64 * TJ) void reverse_tile_kernel(Dims d, RevCoef c
     struct Halo {
         double v[5];
     };
+    // the slot's five values: T, lambda_u .. lambda_T, or u, v, w, lambda_p, p.
+    // Every thread loads five (its own cell's where it has no slot): loads
+    // under a condition would be counted as missing in the waits that follow.
+    const double* hsrc[5];
+#pragma unroll
+    for (int m = 0; m < 5; ++m) {
+        const double* a = m == 0 ? q + FT * sf : lam + m * sf;
+        const double* b = m < 3 ? q + (FU + m) * sf : (m == 3 ? lam : q);
+        hsrc[m] = reinterpret_cast<const double*>(reinterpret_cast<const char*>(hkind == 1 ? a : b) + ohalo);
+    }
     auto load_halo = [&](int k, Halo& H) __attribute__((always_inline)) {
         const long long kz = (k + NG) * Z;
-        if (hkind == 1) {
-            H.v[0] = ldo(q + FT * sf + kz, ohalo);
 #pragma unroll
-            for (int f = FU; f <= FT; ++f) H.v[f] = ldo(lam + f * sf + kz, ohalo);
-        } else if (hkind >= 0) {
-            H.v[0] = ldo(q + FU * sf + kz, ohalo);
-            H.v[1] = ldo(q + FV * sf + kz, ohalo);
-            H.v[2] = ldo(q + FW * sf + kz, ohalo);
-            H.v[3] = ldo(lam + FP * sf + kz, ohalo);
-            H.v[4] = ldo(q + FP * sf + kz, ohalo);
-        }
+        for (int m = 0; m < 5; ++m) H.v[m] = hsrc[m][kz];
     };
     auto store_halo = [&](const Halo& H, double* B, double* Q) __attribute__((always_inline)) {
         if (hkind == 1) {
@@ -399,6 +409,10 @@ __global__ __launch_bounds__(64 * TJ) void reverse_tile_kernel(Dims d, RevCoef c
     Col cur, nxt, nn2;
     Halo H;
     double* const Q0 = L + 2 * RT::TWO;
+    // the hot-wall temperature of this row, loaded a plane ahead
+    const double* const wsrc = c.t_hot_field ? c.t_hot_field + jc : q;
+    const long long wstep = c.t_hot_field ? d.nj : 0;
+    double wall = wsrc[k0 * wstep];
     load(k0, cur);
     load_l(k0, cur);
     load_halo(k0, H);
@@ -426,12 +440,18 @@ __global__ __launch_bounds__(64 * TJ) void reverse_tile_kernel(Dims d, RevCoef c
     derive(cur, Q0);
     if (k0 + 1 < nk) derive(nxt, Q0 + RT::THREE);
     double acc_ra = 0.0, acc_s = 0.0;
+    // the last plane the chunk needs; loads past it repeat it (a load under a
+    // condition would be waited for at once, to be merged with the old value)
+    const int klast = min(k1 + 1, nk - 1);
 
     // One plane per iteration; the sets of planes k, k+1, k+2 are moved down
     // once their values have arrived and the next loads go straight into
     // their set (unrolled by three with rotating sets the kernel spilled 44
     // registers: the LDS addresses of three planes, held across the loop).
     int oq = 0, oqn = RT::THREE, oqnn = 2 * RT::THREE;
+    // all loads so far done (vmcnt 0): were some still in flight here, every
+    // iteration would start with a wait for them, and with it for its own
+    __builtin_amdgcn_s_waitcnt(0x0f70);
     for (int k = k0; k < k1; ++k) {
         double* const B = L + ((k - k0) & 1) * RT::TWO;
         double* const Q = Q0 + oq;
@@ -445,8 +465,10 @@ __global__ __launch_bounds__(64 * TJ) void reverse_tile_kernel(Dims d, RevCoef c
         for (int f = 0; f < 4; ++f) B[o1 + (RT::LU + f) * RT::S1] = cur.l[f];
         B[op] = cur.p;
         store_halo(H, B, Q);
-        if (k + 1 < k1) load_halo(k + 1, H);
+        load_halo(min(k + 1, k1 - 1), H);
         __syncthreads();
+
+        const double tw = c.t_hot_field ? wall : c.t_hot;
 
         // e's own terms, then axis by axis the stars landing on e and e's own
         const double dt = Q[o1 + RT::DT * RT::S1], f0[NF - 1] = {cur.u, cur.v, cur.w, cur.t};
@@ -489,13 +511,13 @@ __global__ __launch_bounds__(64 * TJ) void reverse_tile_kernel(Dims d, RevCoef c
             if (!bnd || x >= 2) a.Lp -= Q[oX - 2 * dX];
             if (!bnd || x < n - 2) a.Lp -= Q[oX + 2 * dX];
             double pl = B[op - dp], ph = B[op + dp], pl2 = B[op - 2 * dp], ph2 = B[op + 2 * dp];
-            if (bnd) axis_ghosts<AX>(c, d, x, n, jc, k, f0, cur.p, fl, fh, pl, ph, pl2, ph2);
+            if (bnd) axis_ghosts<AX>(c, x, n, tw, f0, cur.p, fl, fh, pl, ph, pl2, ph2);
             r.axis<AX>(c, cur.l, f0, cur.p, fl, fh, pl, ph, pl2, ph2);
             PHASE();
         };
         in_plane(std::integral_constant<int, 0>{}, i, d.ni, bnd_i, 1, 1, ox, 1);
         in_plane(std::integral_constant<int, 1>{}, j, d.nj, bnd_j, RT::W1, RT::WP, oy, 64);
-        if (k + 2 < nk) derive(nn2, Qnn);
+        derive(nn2, Qnn);
         me.X = cur.X;
         me.s = cur.w * c.hz2;
         {
@@ -509,7 +531,7 @@ __global__ __launch_bounds__(64 * TJ) void reverse_tile_kernel(Dims d, RevCoef c
             if (k < nk - 2) a.Lp -= nn2.X;
             if (k <= 1) add_wall<2, -1>(a, c, k, nk, k == 0 ? me : prv, k == 0 ? hi.X : me.X, nullptr);
             if (k >= nk - 2) add_wall<2, 1>(a, c, k, nk, k == nk - 1 ? me : hi, k == nk - 1 ? prv.X : me.X, nullptr);
-            if (k <= 1 || k >= nk - 2) axis_ghosts<2>(c, d, k, nk, jc, k, f0, cur.p, fm, fh, pm, ph, pm2, ph2);
+            if (k <= 1 || k >= nk - 2) axis_ghosts<2>(c, k, nk, 0.0, f0, cur.p, fm, fh, pm, ph, pm2, ph2);
             r.axis<2>(c, cur.l, f0, cur.p, fm, fh, pm, ph, pm2, ph2);
         }
         PHASE();
@@ -532,18 +554,27 @@ __global__ __launch_bounds__(64 * TJ) void reverse_tile_kernel(Dims d, RevCoef c
             for (int f = 0; f < NF; ++f)
                 __builtin_nontemporal_store(v[f], reinterpret_cast<double*>(reinterpret_cast<char*>(out + f * sf + kz) + ocol));
         }
-        xm2 = pX;
-        pX = cur.X;
+        // Move the sets down a plane, before the next loads are issued: left to
+        // the end of the loop, these copies make the loads write elsewhere, and
+        // be waited for at once, to be copied in their turn.
+        xm2 = moved(pX);
+        pX = moved(cur.X);
         pBp = me.Bp;
 #pragma unroll
         for (int f = 0; f < NF - 1; ++f) pa[f] = cur.l[f] * dt;
-        fm[0] = cur.u; fm[1] = cur.v; fm[2] = cur.w; fm[3] = cur.t;
-        pm2 = pm;
-        pm = cur.p;
-        cur = nxt;
-        nxt.u = nn2.u; nxt.v = nn2.v; nxt.w = nn2.w; nxt.p = nn2.p; nxt.lp = nn2.lp; nxt.X = nn2.X;
-        if (k + 2 < nk && k + 1 < k1) load_l(k + 2, nxt);
-        if (k + 3 < nk && k + 1 < k1) load(k + 3, nn2);
+        fm[0] = moved(cur.u); fm[1] = moved(cur.v); fm[2] = moved(cur.w); fm[3] = moved(cur.t);
+        pm2 = moved(pm);
+        pm = moved(cur.p);
+        cur.u = moved(nxt.u); cur.v = moved(nxt.v); cur.w = moved(nxt.w); cur.t = moved(nxt.t);
+        cur.p = moved(nxt.p); cur.lp = moved(nxt.lp); cur.X = moved(nxt.X);
+#pragma unroll
+        for (int f = 0; f < NF - 1; ++f) cur.l[f] = moved(nxt.l[f]);
+        nxt.u = moved(nn2.u); nxt.v = moved(nn2.v); nxt.w = moved(nn2.w);
+        nxt.p = moved(nn2.p); nxt.lp = moved(nn2.lp); nxt.X = moved(nn2.X);
+        PHASE();
+        wall = wsrc[min(k + 1, k1 - 1) * wstep];
+        load_l(min(k + 2, klast), nxt);
+        load(min(k + 3, klast), nn2);
         const int t3 = oq;
         oq = oqn;
         oqn = oqnn;
