@@ -73,10 +73,12 @@ struct SweepGeom {
     bool point, point_norm;   // the step without / with norms runs one cell per thread
     int npart;                // norm partials of the step with norms
 };
-// slots: blocks resident at once; ti x tj: the tile of the launch
-SweepGeom sweep_geom(const Dims& d, int slots, int ti = SW_TI, int tj = SW_TJ);
+// ti x tj: the tile of the launch; per_cu: its blocks resident at once per
+// compute unit; streams_f64: an FP64 launch that moves the state at the
+// memory's pace (the step), not its blocks' own
+SweepGeom sweep_geom(const Dims& d, int cus, int ti = SW_TI, int tj = SW_TJ, int per_cu = 1, bool streams_f64 = false);
 // Tile of the single-cavity step sweep in FP32: 32 x 8 threads, four
-// wavefronts, so that four blocks stay resident per compute unit at that
+// wavefronts, so that three blocks stay resident per compute unit at that
 // kernel's register count (FP64 keeps SW_TI x SW_TJ, one block of eight).
 constexpr int F32_TI = 32, F32_TJ = 8;
 constexpr int F64_TI = 64, F64_TJ = 8;

@@ -21,9 +21,9 @@
 namespace cav {
 
 // Tile of the step sweep: FP64 64 x 8 (eight wavefronts; at its register
-// count, 199, one block per compute unit), FP32 32 x 8 (four wavefronts; 123
-// registers, four resident blocks per compute unit, whose barriers
-// interleave).
+// count, 196, one block per compute unit), FP32 32 x 8 (four wavefronts; 135
+// registers, three resident blocks per compute unit, whose barriers
+// interleave; 126 and four blocks measured the same).
 template <typename Real>
 struct StepTile {
     static constexpr int TI = sizeof(Real) == 4 ? F32_TI : F64_TI;
@@ -122,12 +122,12 @@ __global__ __launch_bounds__(StepTile<Real>::THREADS) void sweep_kernel(
 // ---------------------------------------------------------------------------
 // The step of a small grid: one cell per thread, its star read straight from
 // global memory (L2 and the memory-side cache hold the state), no k march.
-// A launch of the marching tile lasts ~9 us (FP64) however few planes its
+// A launch of the marching tile lasts ~8 us (FP64) however few planes its
 // blocks march: start-up of the queues and planes, then a chain of barriers.
 // Here the chain is one round of independent loads, one residual and the
 // stores.  Per step, without norms, marching tile -> this kernel: FP64 16^3
-// 9.2 -> 4.5 us, 48^3 9.6 -> 6.3, 96^3 24.7 -> 21.4; FP32 16^3 6.0 -> 3.5,
-// 64^3 7.3 -> 5.4, 160^3 45.7 -> 38.
+// 8.2 -> 4.5 us, 48^3 8.2 -> 5.9, 80^3 18.3 -> 14.9; FP32 16^3 6.0 -> 3.5,
+// 64^3 7.3 -> 5.6, 160^3 44 -> 39.
 //
 // A block is CELLS cells, consecutive in (k, j, i) order whatever the extents
 // (no idle lanes at ragged ones), and one more wavefront that updates the
@@ -264,25 +264,33 @@ hipError_t launch_math(const double* x, double* out, int n, hipStream_t s)
     return hipGetLastError();
 }
 
-SweepGeom sweep_geom(const Dims& d, int slots, int ti, int tj)
+SweepGeom sweep_geom(const Dims& d, int cus, int ti, int tj, int per_cu, bool streams_f64)
 {
     SweepGeom g;
     g.tiles_i = (d.ni + ti - 1) / ti;
     g.tiles_j = (d.nj + tj - 1) / tj;
-    const int tiles = g.tiles_i * g.tiles_j;
+    const int tiles = g.tiles_i * g.tiles_j, slots = cus * per_cu;
     // Split the k columns into nkc chunks so that the launch finishes
     // earliest: blocks run in rounds of `slots` (the blocks resident at
-    // once), a block costs its planes plus ~3 planes of start-up
-    // (the queue and halo planes it loads before its first plane).
+    // once), a block costs its planes plus ~3 planes of start-up (the queue
+    // and halo planes it loads before its first plane).  An FP64 sweep whose
+    // two states exceed the memory-side cache is bound by HBM, which four
+    // fifths of the blocks keep busy: there the planes of all blocks count,
+    // until the rounds at that rate take longer (192^3: 3 chunks 117 us, the 7
+    // that minimise the rounds 123; 224^3 187 against 202; 144x150x160 71
+    // against 70).  In FP32, with three blocks per CU, the rule does harm
+    // (176^3 68 against 62 us, 224^3 121 against 109; 256^3 142 against 152).
     const int overhead = 3;
-    long long best_cost = -1;
+    const bool hbm = streams_f64 && 2.0 * NF * sizeof(double) * d.ni * d.nj * d.nk > 192e6;
+    double best_cost = -1.0;
     int best = 1;
     const int max_nkc = max(1, d.nk / CAV_MIN_KC);
     for (int nkc = 1; nkc <= max_nkc; ++nkc) {
         const int kc = (d.nk + nkc - 1) / nkc;
         const long long blocks = (long long)tiles * ((d.nk + kc - 1) / kc);
         const long long rounds = (blocks + slots - 1) / slots;
-        const long long cost = rounds * (kc + overhead);
+        double cost = (double)rounds * (kc + overhead) * slots;
+        if (hbm) cost = fmax(0.8 * cost, (double)blocks * (kc + overhead));
         if (best_cost < 0 || cost < best_cost) {
             best_cost = cost;
             best = nkc;
@@ -310,22 +318,23 @@ SweepGeom tile_geom(const Dims& d, int cus)
             n = 1;
         per_cu = n;
     }
-    return sweep_geom(d, cus * per_cu, StepTile<Real>::TI, StepTile<Real>::TJ);
+    return sweep_geom(d, cus, StepTile<Real>::TI, StepTile<Real>::TJ, per_cu, sizeof(Real) == 8);
 }
 template SweepGeom tile_geom<double>(const Dims&, int);
 template SweepGeom tile_geom<float>(const Dims&, int);
 
 // The tile, or one cell per thread where that is faster.  FP32: while both
-// states stay in the 256 MB memory-side cache (160^3, 164 MB: 38 against 46
-// us; 176^3, 218 MB: 59-66 against 63 us).  FP64: by both kernels' measured
-// cost in us: the tile 2.0 a plane of its blocks, with 2.2 planes of start-up
-// (80^3 20, 96^3 25, 128^3 42, 161x97x130 47), the other 4 + 21 per million
-// cells (15, 21, 46, 46); they cross between 96^3 and 128^3, later where the
-// extents leave lanes of the tile idle.  (A grid of 4.2 million cells has at
-// most 48 (FP64) or 96 (FP32) padded elements a cell, so that kernel's byte
-// offsets fit in 32 bits.)  With norms only up to 150 thousand cells: each
-// wavefront's five butterflies cost as much as its residual (161x97x130: 190
-// us against the tile's 125 for a step, its norms and the copy back).
+// states stay in the 256 MB memory-side cache (160^3, 164 MB: 39 against 44
+// us; 176^3, 218 MB: 59-66 against 62 us).  FP64: by both kernels' measured
+// cost in us: the tile 4.9 + 1.65 a plane of its blocks (48^3 8.2, 72^3 14.7,
+// 96^3 22.1, 161x97x130 42.2, 144x150x160 71), the other 4 + 21 per million
+// cells (5.9, 12.7, 21.4, 45.6, 101); they cross twice, near 56^3, where the
+// tile's chunks reach their shortest, and near 90^3.  (A grid of 4.2 million
+// cells has at most 48 (FP64) or 96 (FP32) padded elements a cell, so that
+// kernel's byte offsets fit in 32 bits.)  With norms only up to 150 thousand
+// cells: each wavefront's five butterflies cost as much as its residual
+// (161x97x130: 190 us against the tile's 125 for a step, its norms and the
+// copy back).
 template <typename Real>
 SweepGeom step_geom(const Dims& d, int cus)
 {
@@ -334,7 +343,7 @@ SweepGeom step_geom(const Dims& d, int cus)
     constexpr int CELLS = PointSweep<Real, true, false>::CELLS;
     const int rounds = (g.nblocks + cus - 1) / cus;
     g.point = sizeof(Real) == 4 ? n <= 4200000
-                                : n <= 4200000 && 4.0 + 21e-6 * (double)n < 1.0 + 2.0 * rounds * (g.kc + 2.2);
+                                : n <= 4200000 && 4.0 + 21e-6 * (double)n < 4.9 + 1.65 * rounds * g.kc;
     g.point_norm = g.point && n <= 150000;
     if (g.point_norm) g.npart = (int)((n + CELLS - 1) / CELLS);
     return g;

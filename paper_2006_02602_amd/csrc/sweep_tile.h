@@ -98,17 +98,15 @@ struct OwnAll {
 // are updated (and enter the norm).  Used by the single-cavity sweep, the
 // batched kernel and the interior/exterior split.  The block has TI x TJ =
 // 512 or 256 threads, launched as SW_TI x (TI TJ / SW_TI): thread t = lane +
-// TI * row works on column (i0 + lane, j0 + row); TI >= 16 and TJ >= 4 (the
-// halo roles below need 12 threads per row; 4-row tiles give each thread
-// two of the eight u v w T halo rows).
+// TI * row works on column (i0 + lane, j0 + row).
 template <typename Real, bool NORM, typename Own, typename Epi, int TI = SW_TI, int TJ = SW_TJ>
 __device__ __forceinline__ void sweep_tile(const Dims& d, const CoefR<Real>& c, const TileBox& tb, const Own& own,
                                            const CStateT<Real>& q, Epi& epi, double* partials,
                                            SweepLds<Real, TI, TJ>& L)
 {
-    static_assert((TI * TJ == 512 || TI * TJ == 256) && TI >= 16 && (TJ >= 8 || TJ == 4),
-                  "512- or 256-thread tiles, TI >= 16, TJ = 4 or >= 8");
-    constexpr int UR = TJ >= 8 ? 1 : 2;            // u v w T halo rows per thread
+    constexpr int THREADS = TI * TJ;
+    static_assert((THREADS == 512 || THREADS == 256) && TJ >= 8 && 4 * TI + 12 * TJ <= THREADS,
+                  "512- or 256-thread tiles whose halo is two loads a thread");
     using Lds = SweepLds<Real, TI, TJ>;
     constexpr int PW = Lds::PW, UW = Lds::UW;
     constexpr int PPL = Lds::PPL, UPL = Lds::UPL;
@@ -123,65 +121,66 @@ __device__ __forceinline__ void sweep_tile(const Dims& d, const CoefR<Real>& c, 
     const int lane = TI == SW_TI ? (int)threadIdx.x : tid % TI;
     const int row = TI == SW_TI ? (int)threadIdx.y : tid / TI;
     const int i = i0 + lane, j = j0 + row;
-    // columns no owned cell's star reaches are neither loaded nor computed
+    // columns no owned cell's star reaches are not computed
     const bool active = i < d.ni && j < d.nj && own.column(i, j);
 
-
     // ---- what this thread loads (fixed for the whole march) ----
-    // Only interior cells are loaded.  LDS cells beyond a wall hold zeros and
-    // are read only into star values that star_ghosts_axis then replaces; the
-    // k neighbours beyond the z walls come by recurrences on the queues.
+    // Per plane every thread loads the five fields of its column and two halo
+    // values, whatever its place: threads past the grid, or with no halo value
+    // of their own, repeat a neighbour's address.  A load under a condition
+    // would be taken as not issued by the waits that follow it, which then
+    // wait for younger loads too and undo the look-ahead.  Only interior cells
+    // are loaded.  LDS cells beyond a wall are read only into star values that
+    // star_ghosts_axis then replaces; the k neighbours beyond the z walls come
+    // by recurrences on the queues.
     auto interior = [&](int ii, int jj) { return ii >= 0 && ii < d.ni && jj >= 0 && jj < d.nj; };
-    // p rows j0-2, j0-1, j0+TJ, j0+TJ+1: waves 0..3, one row each
-    const bool has_prow = row < 4;
-    const int prow_lds = row < 2 ? row : TJ + row;
-    const int prow_j = j0 - 2 + prow_lds;
-    const bool ld_prow = has_prow && interior(i, prow_j) && own.column(i, prow_j);
-    // u v w T rows j0-1, j0+TJ: slot s = 0..7 is field 1 + s/2, side s&1;
-    // this thread's slots are row (and row + 4 in 4-row tiles)
-    bool has_urow[UR], ld_urow[UR];
-    int urow_dst[UR], off_urow[UR];
-    const Real* URg[UR];
-#pragma unroll
-    for (int r = 0; r < UR; ++r) {
-        const int sl = row + 4 * r;
-        has_urow[r] = sl < 8;
-        const int uf = FU + (min(sl, 7) >> 1);
-        const int ul = (sl & 1) ? TJ + 1 : 0;
-        const int uj = j0 - 1 + ul;
-        ld_urow[r] = has_urow[r] && interior(i, uj) && own.column(i, uj);
-        urow_dst[r] = (uf - FU) * UPL + ul * UW + lane + 1;
-        off_urow[r] = cell_off(d, i, uj, 0);
-        URg[r] = q.f[uf];
+    const int off_c = cell_off(d, min(i, d.ni - 1), min(j, d.nj - 1), 0);
+    const long long fs = q.f[FU] - q.f[FP];          // elements per field
+    // halo value A: u v w T rows j0-1, j0+TJ, slot s = tid / TI = 0..7 is
+    // field 1 + s/2, side s&1
+    const Real* srcA = q.f[FP] + off_c;
+    bool hasA = false;
+    int dstA = 0;
+    if (tid < 8 * TI) {
+        const int sl = tid / TI, ul = (sl & 1) ? TJ + 1 : 0, uj = j0 - 1 + ul, ui = i0 + tid % TI;
+        hasA = interior(ui, uj) && own.column(ui, uj);
+        dstA = (sl >> 1) * UPL + ul * UW + tid % TI + 1;
+        if (hasA) srcA = q.f[FP] + (FU + (sl >> 1)) * fs + cell_off(d, ui, uj, 0);
     }
-    // column halos of this wave's row: lanes 0..3 p (i0-2, i0-1, i0+TI,
-    // i0+TI+1), lanes 4..11 u v w T (i0-1, i0+TI)
-    const bool has_col = lane < 12;
-    int col_f, col_lds, col_i;
-    if (lane < 4) {
-        col_f = FP;
-        const int cc = lane < 2 ? lane : TI + lane;
-        col_i = i0 - 2 + cc;
-        col_lds = (row + 2) * PW + cc;
-    } else {
-        const int t = min(lane - 4, 7);
-        col_f = FU + (t >> 1);
-        const int cc = (t & 1) ? TI + 1 : 0;
-        col_i = i0 - 1 + cc;
-        col_lds = (col_f - FU) * UPL + (row + 1) * UW + cc;
+    // halo value B: p rows j0-2, j0-1, j0+TJ, j0+TJ+1, then the columns: per
+    // row, p at i0-2, i0-1, i0+TI, i0+TI+1 and u v w T at i0-1, i0+TI
+    const Real* srcB = q.f[FP] + off_c;
+    bool hasB = false, pB = true;
+    int dstB = 0;
+    if (tid < 4 * TI) {
+        const int r = tid / TI, pl = r < 2 ? r : TJ + r, pj = j0 - 2 + pl, pi = i0 + tid % TI;
+        hasB = interior(pi, pj) && own.column(pi, pj);
+        dstB = pl * PW + tid % TI + 2;
+        if (hasB) srcB = q.f[FP] + cell_off(d, pi, pj, 0);
+    } else if (tid < 4 * TI + 12 * TJ) {
+        const int h = tid - 4 * TI, r = h / 12, m = h % 12;
+        int f = FP, cc, ci;
+        if (m < 4) {
+            cc = m < 2 ? m : TI + m;
+            ci = i0 - 2 + cc;
+            dstB = (r + 2) * PW + cc;
+        } else {
+            const int t = m - 4;
+            f = FU + (t >> 1);
+            cc = (t & 1) ? TI + 1 : 0;
+            ci = i0 - 1 + cc;
+            dstB = (t >> 1) * UPL + (r + 1) * UW + cc;
+            pB = false;
+        }
+        hasB = interior(ci, j0 + r);
+        if (hasB) srcB = q.f[FP] + f * fs + cell_off(d, ci, j0 + r, 0);
     }
-    const bool ld_col = has_col && interior(col_i, j);
-    const int prow_dst = prow_lds * PW + lane + 2;
-    const int off_c = cell_off(d, i, j, 0);
-    const int off_prow = cell_off(d, i, prow_j, 0);
-    const int off_col = cell_off(d, col_i, j, 0);
-    const Real* const Pg = q.f[FP];
-    const Real* const Ug = q.f[FU];
-    const Real* const Vg = q.f[FV];
-    const Real* const Wg = q.f[FW];
-    const Real* const Tg = q.f[FT];
-    const Real* const COLg = q.f[col_f];
-    const int Z = d.sz;
+    const Real* const Pg = q.f[FP] + off_c;
+    const Real* const Ug = q.f[FU] + off_c;
+    const Real* const Vg = q.f[FV] + off_c;
+    const Real* const Wg = q.f[FW] + off_c;
+    const Real* const Tg = q.f[FT] + off_c;
+    const long long Z = d.sz;
 
     // tiles whose stars reach past an i or j wall (block-uniform)
     const bool bnd_i = i0 == 0 || i0 + TI + 2 > d.ni, bnd_j = j0 == 0 || j0 + TJ + 2 > d.nj;
@@ -195,17 +194,13 @@ __device__ __forceinline__ void sweep_tile(const Dims& d, const CoefR<Real>& c, 
         // planes k0-2 .. k0+1 of this column; planes beyond the z walls
         // follow from the wall rules (recurrences along k)
         Real P[4], U[2], V[2], W[2], T[2];
-        for (int m = 0; m < 4; ++m) {
-            const int kk = k0 - 2 + m;
-            P[m] = (active && kk >= 0 && kk < d.nk) ? Pg[off_c + kk * Z] : Real(0);
-        }
+        for (int m = 0; m < 4; ++m) P[m] = Pg[max(0, min(k0 - 2 + m, d.nk - 1)) * Z];
         for (int m = 0; m < 2; ++m) {
-            const int kk = k0 - 1 + m;
-            const bool in = active && kk >= 0;
-            U[m] = in ? Ug[off_c + kk * Z] : Real(0);
-            V[m] = in ? Vg[off_c + kk * Z] : Real(0);
-            W[m] = in ? Wg[off_c + kk * Z] : Real(0);
-            T[m] = in ? Tg[off_c + kk * Z] : Real(0);
+            const long long kz = max(0, k0 - 1 + m) * Z;
+            U[m] = Ug[kz];
+            V[m] = Vg[kz];
+            W[m] = Wg[kz];
+            T[m] = Tg[kz];
         }
         if (k0 + 1 >= d.nk) P[3] = Real(2) * P[2] - P[1];
         for (int m = 1; m >= 0; --m)
@@ -220,39 +215,29 @@ __device__ __forceinline__ void sweep_tile(const Dims& d, const CoefR<Real>& c, 
     sU[1 * UPL + lc_u] = v1;
     sU[2 * UPL + lc_u] = w1;
     sU[3 * UPL + lc_u] = t1;
-    if (has_prow) sP[prow_dst] = ld_prow ? Pg[off_prow + k0 * Z] : Real(0);
-#pragma unroll
-    for (int r = 0; r < UR; ++r)
-        if (has_urow[r]) sU[urow_dst[r]] = ld_urow[r] ? URg[r][off_urow[r] + k0 * Z] : Real(0);
-    if (has_col) (col_f == FP ? sP : sU)[col_lds] = ld_col ? COLg[off_col + k0 * Z] : Real(0);
+    if (hasA) sU[dstA] = srcA[k0 * Z];
+    if (hasB) (pB ? sP : sU)[dstB] = srcB[k0 * Z];
 
     // Loads run two planes ahead: what the iteration for plane k needs from
-    // memory (queue heads p(k+2), uvwT(k+1), halo strips of plane k+1) is
+    // memory (queue heads p(k+2), uvwT(k+1), halo values of plane k+1) is
     // issued while plane k-2 is computed; two register sets alternate.
     struct InFlight {
-        Real p, u, v, w, t, prow, urow[UR], col;
+        Real p, u, v, w, t, a, b;
     };
+    const int kp = min(k1 + 1, d.nk - 1), ku = min(k1, d.nk - 1), kh = k1 - 1;   // last planes needed
     auto issue = [&](InFlight& F, int k) __attribute__((always_inline)) {
-        if (active) {
-            if (k + 2 < d.nk) F.p = Pg[off_c + (k + 2) * Z];
-            if (k + 1 < d.nk) {
-                F.u = Ug[off_c + (k + 1) * Z];
-                F.v = Vg[off_c + (k + 1) * Z];
-                F.w = Wg[off_c + (k + 1) * Z];
-                F.t = Tg[off_c + (k + 1) * Z];
-            }
-        }
-        if (k + 1 < k1) {
-            if (ld_prow) F.prow = Pg[off_prow + (k + 1) * Z];
-#pragma unroll
-            for (int r = 0; r < UR; ++r)
-                if (ld_urow[r]) F.urow[r] = URg[r][off_urow[r] + (k + 1) * Z];
-            if (ld_col) F.col = COLg[off_col + (k + 1) * Z];
-        }
+        F.p = Pg[min(k + 2, kp) * Z];
+        const long long kz = min(k + 1, ku) * Z, hz = min(k + 1, kh) * Z;
+        F.u = Ug[kz];
+        F.v = Vg[kz];
+        F.w = Wg[kz];
+        F.t = Tg[kz];
+        F.a = srcA[hz];
+        F.b = srcB[hz];
     };
-    InFlight X{}, Y{};
+    InFlight X, Y;
     issue(X, k0);
-    if (k0 + 1 < k1) issue(Y, k0 + 1);
+    issue(Y, k0 + 1);
     // the epilogue's per-block setup (for the step: the centre cell's new
     // pressure, a star gathered from L2) overlaps the loads in flight
     epi.prepare(d, q, c);
@@ -276,13 +261,10 @@ __device__ __forceinline__ void sweep_tile(const Dims& d, const CoefR<Real>& c, 
             nU[1 * UPL + lc_u] = v2;
             nU[2 * UPL + lc_u] = w2;
             nU[3 * UPL + lc_u] = t2;
-            if (has_prow) nP[prow_dst] = F.prow;
-#pragma unroll
-            for (int r = 0; r < UR; ++r)
-                if (has_urow[r]) nU[urow_dst[r]] = F.urow[r];
-            if (has_col) (col_f == FP ? nP : nU)[col_lds] = F.col;
+            if (hasA) nU[dstA] = F.a;
+            if (hasB) (pB ? nP : nU)[dstB] = F.b;
         }
-        if (k + 2 < k1) issue(F, k + 2);
+        issue(F, k + 2);
 
         Real* const cP = sP + buf * PPL;
         Real* const cU = sU + buf * 4 * UPL;
@@ -305,7 +287,7 @@ __device__ __forceinline__ void sweep_tile(const Dims& d, const CoefR<Real>& c, 
             if (bnd_j && __any(j < 2 || j >= d.nj - 2)) star_ghosts_axis<1>(j, d.nj, s, c, d, j, k);
             Real R[NF], dt;
             cell_residual(c, s, R, dt);
-            epi.cell(c, s, R, dt, off_c + k * Z, i, j, k, acc);
+            epi.cell(c, s, R, dt, off_c + k * d.sz, i, j, k, acc);
         }
         __syncthreads();
         buf ^= 1;
@@ -313,10 +295,14 @@ __device__ __forceinline__ void sweep_tile(const Dims& d, const CoefR<Real>& c, 
         u0 = u1; u1 = u2; v0 = v1; v1 = v2; w0 = w1; w1 = w2; t0 = t1; t1 = t2;
     };
 
-    for (int k = k0; k < k1; k += 2) {
+    // pairs of planes, then a last odd one (a way out of the middle of the
+    // loop would join its back edge with one set of loads not yet issued)
+    int k = k0;
+    for (; k + 1 < k1; k += 2) {
         plane(X, k);
-        if (k + 1 < k1) plane(Y, k + 1);
+        plane(Y, k + 1);
     }
+    if (k < k1) plane(X, k);
 
     if (NORM) {
         // fixed-order block reduction: butterfly within the wavefront, then
