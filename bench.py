@@ -372,11 +372,12 @@ def overlap_leg(C, torch, grid, prm, splits, widths, steps):
         torch.cuda.synchronize()
         C.cavity_timing_enable(False)
         kt = C.cavity_timing_read()
-        # per launch; within a call the sweep of a split along i packs the
-        # next exchange (sweep_xpack), so only the first step runs the pack
+        # per launch; within a call the sweeps of a split along i do the
+        # exchange (sweep_xchg), so only the first step runs a pack; other
+        # splits pack and unpack in one launch (halo_exchange)
         row["unsplit_kernels"] = {k: {"launches": n, "avg_us": round(1e3 * ms / n, 2)} for k, (n, ms) in sorted(kt.items())
-                                  if k in ("sweep", "sweep_xpack", "sweep_norm", "halo_pack", "halo_unpack")}
-        row["unsplit_exchange_us_per_step"] = round(1e3 * sum(kt[k][1] for k in ("halo_pack", "halo_unpack") if k in kt) / steps, 2)
+                                  if k in ("sweep", "sweep_xchg", "sweep_norm", "halo_pack", "halo_exchange")}
+        row["unsplit_exchange_us_per_step"] = round(1e3 * sum(kt[k][1] for k in ("halo_pack", "halo_exchange") if k in kt) / steps, 2)
         C.cavity_timing_read()
         C.cavity_timing_enable(True)
         cav.step_overlap(steps, comm_stream=comm)
@@ -384,7 +385,7 @@ def overlap_leg(C, torch, grid, prm, splits, widths, steps):
         C.cavity_timing_enable(False)
         kt = C.cavity_timing_read()
         row["split_kernels_us"] = {k: round(1e3 * ms / n, 2) for k, (n, ms) in sorted(kt.items())
-                                   if k in ("interior", "interior_norm", "exterior", "exterior_norm", "halo_pack", "halo_unpack")}
+                                   if k in ("interior", "interior_norm", "exterior", "exterior_norm", "halo_exchange")}
         out.append(row)
         del cav
     return out
@@ -642,7 +643,7 @@ def main():
     t_ev = time.perf_counter() - t0
     C.cavity_timing_enable(False)
     kt = C.cavity_timing_read()
-    sw_keys = ("sweep", "sweep_xpack", "sweep_norm")
+    sw_keys = ("sweep", "sweep_xchg", "sweep_norm")
     sw_n = sum(kt[k][0] for k in sw_keys if k in kt)
     sw_ms = sum(kt[k][1] for k in sw_keys if k in kt) / sw_n
     ncell = grid.ncell

@@ -146,7 +146,9 @@ int cavity_init(const cav_grid* grid, const cav_params* prm, uint64_t seed,
 /* Advance the state `nsteps` >= 0 pseudo-time steps (Sec. 2; Sec. 3.1).
  * Each step, in this order:
  *   1. if halo != NULL: halo_pack into halo_buf, then halo_unpack from it
- *      (all virtual subdomains live in q, so the exchange is a round trip),
+ *      (all virtual subdomains live in q, so the exchange is a round trip).
+ *      The two share a launch; for splits along i only, the sweep takes the
+ *      exchanged cells from halo_buf and packs the next step's exchange,
  *   2. for every interior cell: residuals R_p, R_u, R_v, R_w, R_T of
  *      Eq. 1-3 (second-order central differences; fourth-difference
  *      pressure dissipation), local time step, q' = q + dt*R written to

@@ -219,12 +219,14 @@ size_t halo_elems(const HaloGeom& h)
     return (size_t)(faces_area * h.wsum);
 }
 
-// Whether the sweep's epilogue packs the exchange: a split along i only
-// (every face is an i face, the noncontiguous kind), every column in at most
-// one face box (subdomain extent along i >= 2 x the largest width), buffer
-// offsets within 32 bits.  Other splits keep the pack kernel: there the
-// epilogue's extra stores cost the sweep more than the i faces' pack costs
-// (2x2x2 at 256^3: sweep +33 us for pack -20 us, unpack +10 us).
+// Whether the sweep itself does the exchange: a split along i only (every
+// face is an i face, the noncontiguous kind), every column in at most one
+// face box (subdomain extent along i >= 2 x the largest width), buffer
+// offsets within 32 bits.  Its own loads and stores pass over those lines
+// anyway; a launch that moves 8 or 16 bytes of each is bound by the lines
+// (8x1x1 at 256^3: pack 130 us, unpack 140 us).  Other splits keep a launch:
+// there the sweep's extra stores cost more than the i faces' share of it
+// (2x2x2 at 256^3: +33 us in the sweep for 20 us).
 bool xpack_fusable(const HaloGeom& hg)
 {
     int wmax = 0;
@@ -350,19 +352,19 @@ struct BatchGraph {
     int32_t parity;
 };
 
-int do_halo(const cav_grid* grid, const HaloGeom& hg, void* q, void* buf, bool pack, hipStream_t s,
-            bool timed = true, int first_axis = 0)
+int do_halo(const cav_grid* grid, const HaloGeom& hg, void* q, void* buf, HaloMode mode, hipStream_t s,
+            bool timed = true)
 {
     if (hg.blk_end[2] == 0 || hg.wsum == 0) return CAV_OK;       // nothing to exchange
     const Dims d = dims_of(grid);
     auto launch = [&] {
         return grid->dtype == CAV_F32
-                   ? launch_halo<float>(d, hg, state_of<float>(q, d), static_cast<float*>(buf), pack, s, first_axis)
-                   : launch_halo<double>(d, hg, state_of<double>(q, d), static_cast<double*>(buf), pack, s,
-                                         first_axis);
+                   ? launch_halo<float>(d, hg, state_of<float>(q, d), static_cast<float*>(buf), mode, s)
+                   : launch_halo<double>(d, hg, state_of<double>(q, d), static_cast<double*>(buf), mode, s);
     };
-    hipError_t e = timed ? run(pack ? "halo_pack" : "halo_unpack", s, launch) : launch();
-    return e == hipSuccess ? CAV_OK : hip_fail(pack ? "halo_pack launch" : "halo_unpack launch", e);
+    const char* name = mode == HALO_PACK ? "halo_pack" : (mode == HALO_UNPACK ? "halo_unpack" : "halo_exchange");
+    hipError_t e = timed ? run(name, s, launch) : launch();
+    return e == hipSuccess ? CAV_OK : hip_fail(name, e);
 }
 
 // The pseudo-time steps of cavity_step in element type Real.  The last
@@ -375,13 +377,14 @@ int step_impl(const cav_grid* grid, const cav_params* prm, const cav_halo* halo,
               void* q_tmp, double* partials, double* norms, void* halo_buf, int32_t nsteps, hipStream_t stream,
               bool timed = true)
 {
-    int rc;
+    int rc = CAV_OK;
     const Dims d = dims_of(grid);
     const Coef c = coef_of(grid, prm);
     const SweepGeom g = step_geom<Real>(d, device_slots());
     auto go = [&](const char* name, auto&& launch) { return timed ? run(name, stream, launch) : launch(); };
-    // the sweep of step n packs the i faces of step n+1's exchange when the
-    // split allows (xfuse); that step's pack then moves the j and k faces
+    // split along i only (xfuse): the sweep of step n takes the exchanged
+    // cells from the buffer and packs step n+1's exchange, whose sweep does
+    // the same; only the first step packs by a launch of its own
     const bool xfuse = halo && !g.point && xpack_fusable(hg);
     void* cur = q;
     void* nxt = q_tmp;
@@ -389,15 +392,15 @@ int step_impl(const cav_grid* grid, const cav_params* prm, const cav_halo* halo,
     for (int n = 0; n < nsteps; ++n) {
         // the wall ghosts are derived inside the sweep; no separate pass
         if (halo) {
-            const int first_axis = xfuse && n > 0 ? 1 : 0;
-            if ((rc = do_halo(grid, hg, cur, halo_buf, true, stream, timed, first_axis))) return rc;
-            if ((rc = do_halo(grid, hg, cur, halo_buf, false, stream, timed))) return rc;
+            if (!xfuse) rc = do_halo(grid, hg, cur, halo_buf, HALO_EXCHANGE, stream, timed);
+            else if (n == 0) rc = do_halo(grid, hg, cur, halo_buf, HALO_PACK, stream, timed);
+            if (rc) return rc;
         }
         const bool last = n == nsteps - 1 && norms;
-        const bool xp = xfuse && n < nsteps - 1;
-        e = go(last ? "sweep_norm" : (xp ? "sweep_xpack" : "sweep"), [&] {
+        e = go(last ? "sweep_norm" : (xfuse ? "sweep_xchg" : "sweep"), [&] {
             return launch_sweep<Real>(d, c, g, cstate_of<Real>(cur, d), state_of<Real>(nxt, d), partials, last,
-                                      stream, xp ? &hg : nullptr, xp ? static_cast<Real*>(halo_buf) : nullptr);
+                                      stream, xfuse ? &hg : nullptr, static_cast<Real*>(halo_buf),
+                                      n < nsteps - 1);
         });
         if (e != hipSuccess) return hip_fail("sweep launch", e);
         void* t = cur;
@@ -529,8 +532,7 @@ int overlap_impl(const cav_grid* grid, const cav_params* prm, const HaloGeom& hg
         // the exchange on `comm` once the state is complete
         if ((e = hipEventRecord(ready, stream)) != hipSuccess) return done(hip_fail("event record", e));
         if ((e = hipStreamWaitEvent(comm, ready, 0)) != hipSuccess) return done(hip_fail("stream wait", e));
-        if ((rc = do_halo(grid, hg, cur, halo_buf, true, comm))) return done(rc);
-        if ((rc = do_halo(grid, hg, cur, halo_buf, false, comm))) return done(rc);
+        if ((rc = do_halo(grid, hg, cur, halo_buf, HALO_EXCHANGE, comm))) return done(rc);
         if ((e = hipEventRecord(exchanged, comm)) != hipSuccess) return done(hip_fail("event record", e));
         // interior meanwhile on `stream`, exterior after the exchange
         e = run(last ? "interior_norm" : "interior", stream, [&] {
@@ -722,7 +724,7 @@ int halo_pack(const cav_grid* grid, const cav_halo* halo, const void* q, void* b
     const size_t need = halo_elems(hg) * (size_t)elem_size(grid->dtype);
     if (!q || (need && !buf)) return fail(CAV_EINVAL, "q and buf must not be NULL");
     if (buf_bytes < need) return fail(CAV_ESIZE, "buf_bytes %zu < required %zu", buf_bytes, need);
-    return do_halo(grid, hg, const_cast<void*>(q), buf, true, stream);
+    return do_halo(grid, hg, const_cast<void*>(q), buf, HALO_PACK, stream);
 }
 
 int halo_unpack(const cav_grid* grid, const cav_halo* halo, const void* buf, size_t buf_bytes, void* q,
@@ -734,7 +736,7 @@ int halo_unpack(const cav_grid* grid, const cav_halo* halo, const void* buf, siz
     const size_t need = halo_elems(hg) * (size_t)elem_size(grid->dtype);
     if (!q || (need && !buf)) return fail(CAV_EINVAL, "q and buf must not be NULL");
     if (buf_bytes < need) return fail(CAV_ESIZE, "buf_bytes %zu < required %zu", buf_bytes, need);
-    return do_halo(grid, hg, q, const_cast<void*>(buf), false, stream);
+    return do_halo(grid, hg, q, const_cast<void*>(buf), HALO_UNPACK, stream);
 }
 
 int cavity_residual_norm(const cav_grid* grid, const void* ws, size_t ws_bytes, double* out5, hipStream_t stream)

@@ -157,17 +157,16 @@ hipError_t launch_init(const Dims& d, double t_hot, double t_cold, uint64_t seed
 template <typename Real>
 hipError_t launch_sweep(const Dims& d, const Coef& c, const SweepGeom& g, CStateT<Real> q, StateT<Real> qn,
                         double* partials, bool with_norm, hipStream_t s, const HaloGeom* xh = nullptr,
-                        Real* xbuf = nullptr);
+                        Real* xbuf = nullptr, bool xpack = false);
 hipError_t launch_norm_finalize(const double* partials, int nblocks, double ncell, double* out,
                                 hipStream_t s);
 hipError_t launch_math(const double* x, double* out, int n, hipStream_t s);
 // g comes from step_geom<Real>
 template <typename Real>
 hipError_t launch_stream_copy(const Dims& d, const SweepGeom& g, CStateT<Real> q, StateT<Real> qn, hipStream_t s);
-// first_axis 1: only the j and k faces (their block ranges)
+enum HaloMode { HALO_UNPACK, HALO_PACK, HALO_EXCHANGE };      // EXCHANGE: pack, then unpack, in one launch
 template <typename Real>
-hipError_t launch_halo(const Dims& d, const HaloGeom& h, StateT<Real> q, Real* buf, bool pack,
-                       hipStream_t s, int first_axis = 0);
+hipError_t launch_halo(const Dims& d, const HaloGeom& h, StateT<Real> q, Real* buf, HaloMode mode, hipStream_t s);
 template <typename Real>
 // shapes: the tile shapes among the members (1 wide, 2 narrow, 3 both)
 hipError_t launch_batch(const BatchCav* cavs, const int* segs, const BatchItem* items, int parity, bool with_norm,

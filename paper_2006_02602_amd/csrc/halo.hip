@@ -14,6 +14,11 @@
 // consecutive lanes take consecutive rows, whose buffer entries are
 // adjacent: the buffer side is coalesced, the state side moves one short
 // run per row.  The buffer layout is in halo_layout.h.
+//
+// Where a pack is followed by its unpack with nothing between (the exchange
+// inside a step: all virtual subdomains live in one array), one launch does
+// both: the unpack stores, into the receiver's box, the values the pack has
+// just stored into the buffer, from the same registers.
 #include "cavity_internal.h"
 #include "halo_layout.h"
 
@@ -45,11 +50,11 @@ __device__ __forceinline__ void face_of(const HaloGeom& h, int axis, int fidx, i
     else { a = tr % h.P[0]; b = tr / h.P[0]; c = m; }
 }
 
-template <typename Real, bool PACK>
-__global__ __launch_bounds__(HALO_THREADS) void halo_kernel(Dims d, HaloGeom h, StateT<Real> q, Real* buf, int blk0)
+template <typename Real, HaloMode MODE>
+__global__ __launch_bounds__(HALO_THREADS) void halo_kernel(Dims d, HaloGeom h, StateT<Real> q, Real* buf)
 {
     using R2 = typename Pair<Real>::T;
-    int blk = blockIdx.x + blk0;
+    int blk = blockIdx.x;
     const int axis = blk < h.blk_end[0] ? 0 : (blk < h.blk_end[1] ? 1 : 2);
     if (axis > 0) blk -= h.blk_end[axis - 1];
     const int fidx = blk / h.bpf[axis], fblk = blk - fidx * h.bpf[axis];
@@ -104,7 +109,7 @@ __global__ __launch_bounds__(HALO_THREADS) void halo_kernel(Dims d, HaloGeom h, 
     auto paired = [&](const Real* p) { return axis == 0 && (reinterpret_cast<uintptr_t>(p) % sizeof(R2)) == 0; };
 
     Real v[HALO_ROWS][NF][2];
-    if (PACK) {
+    auto get_state = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int r = 0; r < HALO_ROWS; ++r) {
             if (!ok[r]) continue;
@@ -122,6 +127,27 @@ __global__ __launch_bounds__(HALO_THREADS) void halo_kernel(Dims d, HaloGeom h, 
                 }
             }
         }
+    };
+    auto get_buffer = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < HALO_ROWS; ++r) {
+            if (!ok[r]) continue;
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                const int w = h.w[f];
+                const long long o = bidx(f, r, 0);
+                if (w == 2 && paired(B + o)) {
+                    const R2 x = *reinterpret_cast<const R2*>(B + o);
+                    v[r][f][0] = x.x;
+                    v[r][f][1] = x.y;
+                } else {
+                    if (w > 0) v[r][f][0] = B[o];
+                    if (w > 1) v[r][f][1] = B[bidx(f, r, 1)];
+                }
+            }
+        }
+    };
+    auto put_buffer = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int r = 0; r < HALO_ROWS; ++r) {
             if (!ok[r]) continue;
@@ -140,24 +166,8 @@ __global__ __launch_bounds__(HALO_THREADS) void halo_kernel(Dims d, HaloGeom h, 
                 }
             }
         }
-    } else {
-#pragma unroll
-        for (int r = 0; r < HALO_ROWS; ++r) {
-            if (!ok[r]) continue;
-#pragma unroll
-            for (int f = 0; f < NF; ++f) {
-                const int w = h.w[f];
-                const long long o = bidx(f, r, 0);
-                if (w == 2 && paired(B + o)) {
-                    const R2 x = *reinterpret_cast<const R2*>(B + o);
-                    v[r][f][0] = x.x;
-                    v[r][f][1] = x.y;
-                } else {
-                    if (w > 0) v[r][f][0] = B[o];
-                    if (w > 1) v[r][f][1] = B[bidx(f, r, 1)];
-                }
-            }
-        }
+    };
+    auto put_state = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int r = 0; r < HALO_ROWS; ++r) {
             if (!ok[r]) continue;
@@ -176,25 +186,27 @@ __global__ __launch_bounds__(HALO_THREADS) void halo_kernel(Dims d, HaloGeom h, 
                 }
             }
         }
-    }
+    };
+    if (MODE == HALO_UNPACK) get_buffer();
+    else get_state();
+    if (MODE != HALO_UNPACK) put_buffer();
+    if (MODE != HALO_PACK) put_state();
 }
 
-// first_axis 1 launches only the j- and k-face block ranges (the i faces
-// were packed by the sweep's epilogue).
 template <typename Real>
-hipError_t launch_halo(const Dims& d, const HaloGeom& h, StateT<Real> q, Real* buf, bool pack, hipStream_t s,
-                       int first_axis)
+hipError_t launch_halo(const Dims& d, const HaloGeom& h, StateT<Real> q, Real* buf, HaloMode mode, hipStream_t s)
 {
-    const int blk0 = first_axis > 0 ? h.blk_end[first_axis - 1] : 0;
-    const int nb = h.blk_end[2] - blk0;
+    const int nb = h.blk_end[2];
     if (nb <= 0) return hipSuccess;
-    if (pack)
-        halo_kernel<Real, true><<<nb, HALO_THREADS, 0, s>>>(d, h, q, buf, blk0);
+    if (mode == HALO_PACK)
+        halo_kernel<Real, HALO_PACK><<<nb, HALO_THREADS, 0, s>>>(d, h, q, buf);
+    else if (mode == HALO_UNPACK)
+        halo_kernel<Real, HALO_UNPACK><<<nb, HALO_THREADS, 0, s>>>(d, h, q, buf);
     else
-        halo_kernel<Real, false><<<nb, HALO_THREADS, 0, s>>>(d, h, q, buf, blk0);
+        halo_kernel<Real, HALO_EXCHANGE><<<nb, HALO_THREADS, 0, s>>>(d, h, q, buf);
     return hipGetLastError();
 }
-template hipError_t launch_halo<double>(const Dims&, const HaloGeom&, StateT<double>, double*, bool, hipStream_t, int);
-template hipError_t launch_halo<float>(const Dims&, const HaloGeom&, StateT<float>, float*, bool, hipStream_t, int);
+template hipError_t launch_halo<double>(const Dims&, const HaloGeom&, StateT<double>, double*, HaloMode, hipStream_t);
+template hipError_t launch_halo<float>(const Dims&, const HaloGeom&, StateT<float>, float*, HaloMode, hipStream_t);
 
 }  // namespace cav

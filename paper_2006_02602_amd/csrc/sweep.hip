@@ -31,15 +31,14 @@ struct StepTile {
     static constexpr int THREADS = TI * TJ;
 };
 
-// The step's epilogue with the i-face part of the next exchange's pack
-// (Sec. 4.5: the noncontiguous faces that "Optimized V1" packs), for splits
-// along i only: a lane whose column lies within a face width of a cut also
-// stores the new values of its cell at their places in the halo buffer (the
-// layout of halo_pack), so the next step needs no pack kernel.  The values
-// stored are the very ones written to the new state.  Needs every subdomain
-// extent along i >= 2 x the largest width, so that a column lies in at most
-// one face box.
-struct XPackGeom {
+// The exchange of a split along i only, inside the sweep (Sec. 4.5: the
+// noncontiguous i faces that "Optimized V1" packs).  A lane whose column lies
+// within a face width of a cut takes its column's values from the halo buffer
+// instead of the state (the unpack), and stores the new values of its cell at
+// their places in the buffer as well (the pack of the next step's exchange;
+// the layout is halo_pack's).  Needs every subdomain extent along i >= 2 x the
+// largest width, so that a column lies in at most one face box.
+struct XGeom {
     int ex, pi;          // subdomain extent along i, subdomains along i
     int nj;              // face rows per plane (the split is along i only)
     int area;            // face area nj * nk
@@ -47,18 +46,16 @@ struct XPackGeom {
     int w[NF], wpre[NF];
 };
 
-template <typename Real>
-struct StepXPackEpi : StepEpi<Real> {
-    Real* buf;
-    int dd;          // distance of the column to its cut (< the largest width), or -1: no face
+// A column's place in the buffer.
+struct XColumn {
+    int dd = -1;     // distance of the column to its cut (< the largest width), or -1: no face
     int face;        // 0: the -i face of the column's subdomain, 1: its +i face
     int seg;         // element offset of that face's segment in the buffer
-    XPackGeom x;
 
-    __device__ __forceinline__ void init(const Dims& d, int i)
+    __device__ __forceinline__ void init(const XGeom& x, const Dims& d, int i, int j)
     {
         dd = -1;
-        if (i >= d.ni) return;
+        if (i >= d.ni || j >= d.nj) return;
         int wmax = 0;
 #pragma unroll
         for (int f = 0; f < NF; ++f) wmax = max(wmax, x.w[f]);
@@ -71,6 +68,48 @@ struct StepXPackEpi : StepEpi<Real> {
         // only its -i face)
         seg = (a > 0 ? 2 * a - 1 + face : 0) * x.area * x.wsum;
     }
+    __device__ __forceinline__ bool has(const XGeom& x, int f) const { return dd >= 0 && dd < x.w[f]; }
+    // element of field f at row j, plane k
+    __device__ __forceinline__ int at(const XGeom& x, int f, int j, int k) const
+    {
+        const int w = x.w[f];
+        return seg + x.wpre[f] * x.area + (k * x.nj + j) * w + (face ? w - 1 - dd : dd);
+    }
+};
+
+// The unpack, in the column's loads: planes of this block's own chunk come
+// from the buffer.  (Planes of a neighbouring chunk come from the state, which
+// holds the same values: that chunk's block may already be packing its new
+// ones.  A cell's own place is read before it is written, by this thread.)
+template <typename Real>
+struct ExchangedColumn {
+    StateColumn<Real> s;
+    const Real* buf;
+    XGeom x;
+    XColumn c;
+    int j, k0, k1;
+    __device__ __forceinline__ void init(const Dims& d, const CStateT<Real>& q, const TileBox& tb, int i, int jj, int off)
+    {
+        s.init(d, q, tb, i, jj, off);
+        c.init(x, d, i, jj);
+        j = jj;
+        k0 = tb.k0;
+        k1 = tb.k1;
+    }
+    __device__ __forceinline__ Real operator()(int f, int k) const
+    {
+        const Real* a = s.p[f] + k * s.Z;
+        if (c.has(x, f) && k >= k0 && k < k1) a = buf + c.at(x, f, j, k);
+        return *a;
+    }
+};
+
+// The pack, in the step's epilogue.
+template <typename Real>
+struct StepXPackEpi : StepEpi<Real> {
+    Real* buf;
+    XColumn c;
+    XGeom x;
     __device__ __forceinline__ void cell(const CoefR<Real>&, const Star<Real>& s, const Real R[NF], Real dt, int o,
                                          int, int j, int k, double acc[NF])
     {
@@ -80,42 +119,46 @@ struct StepXPackEpi : StepEpi<Real> {
         for (int f = 0; f < NF; ++f) __builtin_nontemporal_store(nv[f], &this->qn.f[f][o]);
 #pragma unroll
         for (int f = 0; f < NF; ++f) acc[f] = fma((double)R[f], (double)R[f], acc[f]);
-        if (dd < 0) return;
-        const int row = k * x.nj + j;              // (k, j) index on the face
+        if (c.dd < 0) return;
 #pragma unroll
-        for (int f = 0; f < NF; ++f) {
-            const int w = x.w[f];
-            if (dd < w) buf[seg + x.wpre[f] * x.area + row * w + (face ? w - 1 - dd : dd)] = nv[f];
-        }
+        for (int f = 0; f < NF; ++f)
+            if (c.has(x, f)) buf[c.at(x, f, j, k)] = nv[f];
     }
 };
 
 // FIELD = false: the hot wall is the scalar t_hot, known at compile time to
-// need no field loads (the kernel the uniform-wall problem runs).  XP: the
-// epilogue also packs the i faces of the new state into xbuf (geometry xh).
-template <typename Real, bool NORM, bool FIELD, bool XP>
+// need no field loads (the kernel the uniform-wall problem runs).  X: 1 the
+// exchange's unpack in the loads, 2 also the next one's pack in the epilogue
+// (buffer xbuf, geometry xg).
+template <typename Real, bool NORM, bool FIELD, int X>
 __global__ __launch_bounds__(StepTile<Real>::THREADS) void sweep_kernel(
-    Dims d, Coef cd, SweepGeom g, CStateT<Real> q, StateT<Real> qn, double* partials, XPackGeom xg, Real* xbuf)
+    Dims d, Coef cd, SweepGeom g, CStateT<Real> q, StateT<Real> qn, double* partials, XGeom xg, Real* xbuf)
 {
     constexpr int TI = StepTile<Real>::TI, TJ = StepTile<Real>::TJ;
     __shared__ SweepLds<Real, TI, TJ> L;
     CoefR<Real> c = coef_as<Real>(cd);
     if constexpr (!FIELD) c.t_hot_field = nullptr;
     const TileBox tb = tile_box<TI, TJ>(d, g.tiles_i, g.tiles_j, g.kc, xcd_block(blockIdx.x, g.nblocks));
-    if constexpr (XP) {
-        StepXPackEpi<Real> epi;
-        epi.qn = qn;
-        epi.pc_new = Real(0);
-        epi.x = xg;
-        epi.buf = xbuf;
-        const int tid = threadIdx.x + SW_TI * threadIdx.y;
-        epi.init(d, tb.i0 + tid % TI);
-        sweep_tile<Real, NORM, OwnAll, StepXPackEpi<Real>, TI, TJ>(d, c, tb, OwnAll{}, q, epi,
-                                                                                         partials, L);
+    if constexpr (X) {
+        ExchangedColumn<Real> col;
+        col.buf = xbuf;
+        col.x = xg;
+        if constexpr (X == 2) {
+            StepXPackEpi<Real> epi;
+            epi.qn = qn;
+            epi.pc_new = Real(0);
+            epi.x = xg;
+            epi.buf = xbuf;
+            const int tid = threadIdx.x + SW_TI * threadIdx.y;
+            epi.c.init(xg, d, tb.i0 + tid % TI, tb.j0 + tid / TI);
+            sweep_tile<Real, NORM, OwnAll, StepXPackEpi<Real>, TI, TJ>(d, c, tb, OwnAll{}, q, epi, partials, L, col);
+        } else {
+            StepEpi<Real> epi{qn, Real(0)};
+            sweep_tile<Real, NORM, OwnAll, StepEpi<Real>, TI, TJ>(d, c, tb, OwnAll{}, q, epi, partials, L, col);
+        }
     } else {
         StepEpi<Real> epi{qn, Real(0)};
-        sweep_tile<Real, NORM, OwnAll, StepEpi<Real>, TI, TJ>(d, c, tb, OwnAll{}, q, epi,
-                                                                                    partials, L);
+        sweep_tile<Real, NORM, OwnAll, StepEpi<Real>, TI, TJ>(d, c, tb, OwnAll{}, q, epi, partials, L);
     }
 }
 
@@ -312,7 +355,7 @@ SweepGeom tile_geom(const Dims& d, int cus)
     static int per_cu = 0;
     if (per_cu == 0) {
         int n = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sweep_kernel<Real, false, false, false>,
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sweep_kernel<Real, false, false, 0>,
                                                          StepTile<Real>::THREADS, 0) != hipSuccess ||
             n < 1)
             n = 1;
@@ -351,15 +394,13 @@ SweepGeom step_geom(const Dims& d, int cus)
 template SweepGeom step_geom<double>(const Dims&, int);
 template SweepGeom step_geom<float>(const Dims&, int);
 
-// g comes from step_geom<Real>.  xh, xbuf: the i-face pack in the epilogue
-// (both NULL: none; never with the norm pass).
+// g comes from step_geom<Real>.  xh, xbuf: the exchange of a split along i
+// inside the sweep (NULL: none; never with one cell per thread); xpack: with
+// the pack of the next step's exchange (never with norms).
 template <typename Real>
 hipError_t launch_sweep(const Dims& d, const Coef& c, const SweepGeom& g, CStateT<Real> q, StateT<Real> qn,
-                        double* partials, bool with_norm, hipStream_t s, const HaloGeom* xh, Real* xbuf)
+                        double* partials, bool with_norm, hipStream_t s, const HaloGeom* xh, Real* xbuf, bool xpack)
 {
-    dim3 block(SW_TI, StepTile<Real>::THREADS / SW_TI), grid(g.nblocks);
-    XPackGeom xg{};
-    const bool xp = xh && xbuf && !with_norm;
     if (with_norm ? g.point_norm : g.point) {
         const int n = d.ni * d.nj * d.nk;
         const bool small = sizeof(Real) == 8 && n <= 448 * 128;
@@ -374,7 +415,9 @@ hipError_t launch_sweep(const Dims& d, const Coef& c, const SweepGeom& g, CState
 #undef POINT_LAUNCH
         return hipGetLastError();
     }
-    if (xp) {
+    dim3 block(SW_TI, StepTile<Real>::THREADS / SW_TI), grid(g.nblocks);
+    XGeom xg{};
+    if (xh) {
         xg.ex = xh->e[0];
         xg.pi = xh->P[0];
         xg.nj = d.nj;
@@ -385,27 +428,22 @@ hipError_t launch_sweep(const Dims& d, const Coef& c, const SweepGeom& g, CState
             xg.wpre[f] = xh->wpre[f];
         }
     }
-    if (c.t_hot_field) {
-        if (with_norm)
-            sweep_kernel<Real, true, true, false><<<grid, block, 0, s>>>(d, c, g, q, qn, partials, xg, nullptr);
-        else if (xp)
-            sweep_kernel<Real, false, true, true><<<grid, block, 0, s>>>(d, c, g, q, qn, partials, xg, xbuf);
-        else
-            sweep_kernel<Real, false, true, false><<<grid, block, 0, s>>>(d, c, g, q, qn, partials, xg, nullptr);
-    } else {
-        if (with_norm)
-            sweep_kernel<Real, true, false, false><<<grid, block, 0, s>>>(d, c, g, q, qn, partials, xg, nullptr);
-        else if (xp)
-            sweep_kernel<Real, false, false, true><<<grid, block, 0, s>>>(d, c, g, q, qn, partials, xg, xbuf);
-        else
-            sweep_kernel<Real, false, false, false><<<grid, block, 0, s>>>(d, c, g, q, qn, partials, xg, nullptr);
-    }
+    auto go = [&](auto field) {
+        constexpr bool F = decltype(field)::value;
+        if (with_norm && xh) sweep_kernel<Real, true, F, 1><<<grid, block, 0, s>>>(d, c, g, q, qn, partials, xg, xbuf);
+        else if (with_norm) sweep_kernel<Real, true, F, 0><<<grid, block, 0, s>>>(d, c, g, q, qn, partials, xg, xbuf);
+        else if (xh && xpack) sweep_kernel<Real, false, F, 2><<<grid, block, 0, s>>>(d, c, g, q, qn, partials, xg, xbuf);
+        else if (xh) sweep_kernel<Real, false, F, 1><<<grid, block, 0, s>>>(d, c, g, q, qn, partials, xg, xbuf);
+        else sweep_kernel<Real, false, F, 0><<<grid, block, 0, s>>>(d, c, g, q, qn, partials, xg, xbuf);
+    };
+    if (c.t_hot_field) go(std::true_type{});
+    else go(std::false_type{});
     return hipGetLastError();
 }
 template hipError_t launch_sweep<double>(const Dims&, const Coef&, const SweepGeom&, CStateT<double>,
-                                         StateT<double>, double*, bool, hipStream_t, const HaloGeom*, double*);
+                                         StateT<double>, double*, bool, hipStream_t, const HaloGeom*, double*, bool);
 template hipError_t launch_sweep<float>(const Dims&, const Coef&, const SweepGeom&, CStateT<float>,
-                                        StateT<float>, double*, bool, hipStream_t, const HaloGeom*, float*);
+                                        StateT<float>, double*, bool, hipStream_t, const HaloGeom*, float*, bool);
 
 // ---------------------------------------------------------------------------
 // Interior/exterior split (Sec. 4.7): with a halo exchange in the step, the

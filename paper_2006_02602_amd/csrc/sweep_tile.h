@@ -99,10 +99,26 @@ struct OwnAll {
 // batched kernel and the interior/exterior split.  The block has TI x TJ =
 // 512 or 256 threads, launched as SW_TI x (TI TJ / SW_TI): thread t = lane +
 // TI * row works on column (i0 + lane, j0 + row).
-template <typename Real, bool NORM, typename Own, typename Epi, int TI = SW_TI, int TJ = SW_TJ>
+// Where a thread's column comes from: the state.  (A sweep that does the
+// exchange of a split along i has another, sweep.hip.)
+template <typename Real>
+struct StateColumn {
+    const Real* p[NF];
+    long long Z;
+    __device__ __forceinline__ void init(const Dims& d, const CStateT<Real>& q, const TileBox&, int, int, int off)
+    {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) p[f] = q.f[f] + off;
+        Z = d.sz;
+    }
+    __device__ __forceinline__ Real operator()(int f, int k) const { return p[f][k * Z]; }
+};
+
+template <typename Real, bool NORM, typename Own, typename Epi, int TI = SW_TI, int TJ = SW_TJ,
+          typename Column = StateColumn<Real>>
 __device__ __forceinline__ void sweep_tile(const Dims& d, const CoefR<Real>& c, const TileBox& tb, const Own& own,
                                            const CStateT<Real>& q, Epi& epi, double* partials,
-                                           SweepLds<Real, TI, TJ>& L)
+                                           SweepLds<Real, TI, TJ>& L, Column C = Column{})
 {
     constexpr int THREADS = TI * TJ;
     static_assert((THREADS == 512 || THREADS == 256) && TJ >= 8 && 4 * TI + 12 * TJ <= THREADS,
@@ -175,11 +191,7 @@ __device__ __forceinline__ void sweep_tile(const Dims& d, const CoefR<Real>& c, 
         hasB = interior(ci, j0 + r);
         if (hasB) srcB = q.f[FP] + f * fs + cell_off(d, ci, j0 + r, 0);
     }
-    const Real* const Pg = q.f[FP] + off_c;
-    const Real* const Ug = q.f[FU] + off_c;
-    const Real* const Vg = q.f[FV] + off_c;
-    const Real* const Wg = q.f[FW] + off_c;
-    const Real* const Tg = q.f[FT] + off_c;
+    C.init(d, q, tb, i, j, off_c);
     const long long Z = d.sz;
 
     // tiles whose stars reach past an i or j wall (block-uniform)
@@ -194,13 +206,13 @@ __device__ __forceinline__ void sweep_tile(const Dims& d, const CoefR<Real>& c, 
         // planes k0-2 .. k0+1 of this column; planes beyond the z walls
         // follow from the wall rules (recurrences along k)
         Real P[4], U[2], V[2], W[2], T[2];
-        for (int m = 0; m < 4; ++m) P[m] = Pg[max(0, min(k0 - 2 + m, d.nk - 1)) * Z];
+        for (int m = 0; m < 4; ++m) P[m] = C(FP, max(0, min(k0 - 2 + m, d.nk - 1)));
         for (int m = 0; m < 2; ++m) {
-            const long long kz = max(0, k0 - 1 + m) * Z;
-            U[m] = Ug[kz];
-            V[m] = Vg[kz];
-            W[m] = Wg[kz];
-            T[m] = Tg[kz];
+            const int kk = max(0, k0 - 1 + m);
+            U[m] = C(FU, kk);
+            V[m] = C(FV, kk);
+            W[m] = C(FW, kk);
+            T[m] = C(FT, kk);
         }
         if (k0 + 1 >= d.nk) P[3] = Real(2) * P[2] - P[1];
         for (int m = 1; m >= 0; --m)
@@ -226,12 +238,13 @@ __device__ __forceinline__ void sweep_tile(const Dims& d, const CoefR<Real>& c, 
     };
     const int kp = min(k1 + 1, d.nk - 1), ku = min(k1, d.nk - 1), kh = k1 - 1;   // last planes needed
     auto issue = [&](InFlight& F, int k) __attribute__((always_inline)) {
-        F.p = Pg[min(k + 2, kp) * Z];
-        const long long kz = min(k + 1, ku) * Z, hz = min(k + 1, kh) * Z;
-        F.u = Ug[kz];
-        F.v = Vg[kz];
-        F.w = Wg[kz];
-        F.t = Tg[kz];
+        const int kk = min(k + 1, ku);
+        const long long hz = min(k + 1, kh) * Z;
+        F.p = C(FP, min(k + 2, kp));
+        F.u = C(FU, kk);
+        F.v = C(FV, kk);
+        F.w = C(FW, kk);
+        F.t = C(FT, kk);
         F.a = srcA[hz];
         F.b = srcB[hz];
     };
