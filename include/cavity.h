@@ -325,7 +325,11 @@ typedef struct {
     void* q_tmp;            /* device scratch state, same size, distinct    */
     void* ws;               /* device workspace                              */
     size_t ws_bytes;        /* >= cavity_workspace_bytes(grid)               */
-    int32_t kc;             /* k planes per work item, 0 = whole columns    */
+    int32_t kc;             /* k planes per work item (nk or more: whole
+                               columns); 0 = the library's choice for the
+                               whole batch, short for few members, long for
+                               many; the result does not depend on it (norms
+                               to the rounding of their grouping)           */
     int32_t ti;             /* tile width: 0 = the wide shape; CAV_F64:
                                64 = 64 x 8 or 32 = 32 x 16 columns (512
                                threads); CAV_F32: 32 = 32 x 8 or 16 = 16 x

@@ -401,7 +401,8 @@ class Batch:
     persistent launch per step over all members; optional graph replay.
 
     members: list of (Grid, Params), (Grid, Params, kc) or
-    (Grid, Params, kc, ti) with ti the tile width: 0 = the wide shape; FP64
+    (Grid, Params, kc, ti) with kc the k planes per work item (0 = the
+    library's choice) and ti the tile width: 0 = the wide shape; FP64
     64 (64 x 8) or 32 (32 x 16); FP32 32 (32 x 8) or 16 (16 x 16)."""
 
     def __init__(self, members, device: str = "cuda"):

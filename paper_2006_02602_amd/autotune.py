@@ -23,9 +23,9 @@ import torch
 
 from . import BATCH_TILE_WIDTHS, Batch, Grid, Params
 
-KC_CANDIDATES = (4, 8, 16, 32, 0)        # 0 = whole columns (the cavity height per item)
+KC_CANDIDATES = (4, 8, 16, 32, 0)        # 0 = the library's choice for the whole batch
 BLOCK_CANDIDATES = (256, 512, 768, 1024)
-CACHE_VERSION = 3                        # bump when the tile shapes or batch kernels change
+CACHE_VERSION = 4                        # bump when the tile shapes or batch kernels change
 
 
 def ti_candidates(dtype):
@@ -99,7 +99,7 @@ def tune_batch(batch, keys, dtype, steps=8, reps=3, passes=2, cache_path=None):
     """({key: (ti, kc)}, nblocks, timings) for a built batch whose member m
     has shape key keys[m] (its cube edge, say), tuned on the whole batch:
     members of one key share a (tile width, kc); starting from the wide tile
-    with whole columns for every key, each key in turn takes the candidate
+    with the library's chunks for every key, each key in turn takes the candidate
     that steps the whole batch fastest with the others held (coordinate
     descent, `passes` rounds) at the block count that is fastest for the
     starting shapes; the block count is tuned again at the end.
