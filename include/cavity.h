@@ -313,11 +313,13 @@ int cavity_adjoint_step(const cav_grid* grid, const cav_params* prm,
 
 /* ---- batched form: many independent cavities, one launch per step -------
  * A batch advances n cavities of arbitrary sizes and parameters (all of one
- * dtype) together: every step is ONE launch of a persistent kernel whose
- * blocks walk a device work list of (cavity, tile column, k chunk) items,
- * each computed with the per-cell code of cavity_step, so every member's
- * state is bit-identical to advancing it alone, whatever its tile shape and
- * k-chunk length (only the grouping of the norm sums differs).  There is no halo exchange in the batched form. */
+ * dtype) together: every step is ONE launch, of a persistent kernel whose
+ * blocks walk a device work list of (cavity, tile column, k chunk) items or,
+ * where that is cheaper for members that leave kc and ti open, of a block per
+ * 448 cells (then nblocks only applies to the last step, which forms the
+ * norms), each computed with the per-cell code of cavity_step, so every
+ * member's state is bit-identical to advancing it alone, whatever its tile
+ * shape and k-chunk length (only the grouping of the norm sums differs).  There is no halo exchange in the batched form. */
 typedef struct {
     cav_grid grid;          /* member grid; dtype must match the batch      */
     cav_params params;      /* member parameters                             */
@@ -348,7 +350,9 @@ typedef struct {
     int32_t shapes;         /* tile shapes among the members: 1 the wide one
                                only, 2 the narrow one only, 3 both (a batch
                                of one shape runs a kernel compiled for it)   */
-    int32_t reserved;
+    int32_t points;         /* blocks of the launch with one cell per thread
+                               that steps without norms take, 0: the
+                               persistent launch takes them too              */
 } cav_batch;
 
 /* Bytes of the device table for these members (host array of n). */

@@ -305,7 +305,7 @@ int member_ti(const cav_batch_member& m)
 // the best length over 14 mixes of 3 to 96 members (20 % at worst, on the
 // smallest); no other weight of an item's start or of the longest item is
 // closer on average.
-int open_kc(int32_t n, const cav_batch_member* members)
+int open_kc(int32_t n, const cav_batch_member* members, double* planes = nullptr)
 {
     int mx = 0;
     for (int m = 0; m < n; ++m)
@@ -329,7 +329,34 @@ int open_kc(int32_t n, const cav_batch_member* members)
             best_kc = kc;
         }
     }
+    if (planes) *planes = best;
     return best_kc;
+}
+
+// Whether the steps without norms of a batch run one cell per thread instead:
+// where every member leaves its tile and chunk open and, by both launches'
+// measured cost in us, that one is cheaper.  planes: the tiles' cost in
+// planes (open_kc).  FP64: 5 + 27 a million cells (36 where both states of
+// all members exceed the 256 MB memory-side cache) against 2.3 a plane: 8
+// ragged members of 0.75 M cells together 25 against 48 us, 5 of 2.6 M 78
+// against 109, 40 of 4.6 M 175 against 228, 60 of 10 M 369 against 423; 60
+// cubes of 18 M, which fill their tiles, 616 against 530.  FP32: 4 + 14 (18
+// where the states exceed 150 MB) against 3.5 + 0.5 a plane: 3 members of 0.2 M
+// 7.0 against 9.1, 8 of 1.8 M 27 against 32, 16 of 2.4 M 37 against 43, 30 of
+// 4.4 M 72 against 71, 60 of 7.3 M 156 against 113.  (A member's cells and offsets: as in step_geom.)
+bool batch_points(int32_t n, const cav_batch_member* members, double planes)
+{
+    const bool f32 = members[0].grid.dtype == CAV_F32;
+    double cells = 0;
+    for (int m = 0; m < n; ++m) {
+        const cav_grid& g = members[m].grid;
+        const double c = (double)g.ni * g.nj * g.nk;
+        if (members[m].kc || members[m].ti || c > 4200000) return false;
+        cells += c;
+    }
+    const bool cached = cells * 2 * NF * (f32 ? 4 : 8) <= (f32 ? 150e6 : 250e6);
+    return f32 ? 4 + (cached ? 14e-6 : 18e-6) * cells < 3.5 + 0.5 * planes
+               : 5 + (cached ? 27e-6 : 36e-6) * cells < 2.3 * planes;
 }
 
 int check_member(const cav_batch_member& m, int idx, int dtype)
@@ -362,7 +389,10 @@ hipError_t batch_launches(const cav_batch& b, int32_t nsteps, int nblocks, int p
     hipError_t e = hipSuccess;
     for (int n = 0; n < nsteps && e == hipSuccess; ++n) {
         const bool last = n == nsteps - 1;
-        auto go = [&] { return launch_batch<Real>(cavs, segs, items, parity, last, nblocks, b.shapes, stream); };
+        auto go = [&] {
+            return b.points && !last ? launch_batch_points<Real>(cavs, b.members, b.points, parity, stream)
+                                     : launch_batch<Real>(cavs, segs, items, parity, last, nblocks, b.shapes, stream);
+        };
         e = timed ? run(last ? "batch_norm" : "batch", stream, go) : go();
         parity ^= 1;
     }
@@ -898,7 +928,9 @@ int cavity_batch_build(int32_t n, const cav_batch_member* members, void* table, 
     struct Work { BatchItem it; long long cost; };
     std::vector<Work> work;
     uint64_t cells = 0;
-    const int open = open_kc(n, members);
+    int points = 0;
+    double planes = 0;
+    const int open = open_kc(n, members, &planes);
     for (int m = 0; m < n; ++m) {
         const cav_batch_member& mb = members[m];
         const Dims d = dims_of(&mb.grid);
@@ -917,6 +949,8 @@ int cavity_batch_build(int32_t n, const cav_batch_member* members, void* table, 
         cv.q_tmp = mb.q_tmp;
         cv.ws = static_cast<double*>(mb.ws);
         cv.fstride = (long long)field_elems(d);
+        cv.pstart = points;
+        points += (int)(((long long)d.ni * d.nj * d.nk + POINT_CELLS - 1) / POINT_CELLS);
         cells += (uint64_t)d.ni * d.nj * d.nk;
         for (int t = 0; t < g.nblocks; ++t) {
             const int bi = t % g.tiles_i, bj = (t / g.tiles_i) % g.tiles_j, bk = t / (g.tiles_i * g.tiles_j);
@@ -962,7 +996,7 @@ int cavity_batch_build(int32_t n, const cav_batch_member* members, void* table, 
     out->cells = cells;
     out->shapes = 0;
     for (int m = 0; m < n; ++m) out->shapes |= member_ti(members[m]) == batch_wide_ti(dtype == CAV_F32) ? 1 : 2;
-    out->reserved = 0;
+    out->points = batch_points(n, members, planes) ? points : 0;
     return CAV_OK;
 }
 

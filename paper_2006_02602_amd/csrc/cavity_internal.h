@@ -134,6 +134,7 @@ struct BatchCav {
     void* q_tmp;
     double* ws;                           // workspace (norms, then partials)
     long long fstride;                    // elements per field
+    int pstart;                           // the member's first block in the one-cell-per-thread launch
 };
 struct BatchItem {
     int cav, tile;
@@ -172,6 +173,11 @@ template <typename Real>
 hipError_t launch_batch(const BatchCav* cavs, const int* segs, const BatchItem* items, int parity, bool with_norm,
                         int nblocks, int shapes, hipStream_t s);
 hipError_t launch_batch_norms(const BatchCav* cavs, int members, hipStream_t s);
+// The step of a batch (without norms) with one cell per thread: points blocks,
+// POINT_CELLS cells of one member each.
+constexpr int POINT_CELLS = 448;
+template <typename Real>
+hipError_t launch_batch_points(const BatchCav* cavs, int members, int points, int parity, hipStream_t s);
 template <typename Real>
 hipError_t launch_nusselt(const Dims& d, const Bcs& b, CStateT<Real> q, double* out,
                           hipStream_t s);

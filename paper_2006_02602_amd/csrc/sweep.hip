@@ -185,19 +185,18 @@ __global__ __launch_bounds__(StepTile<Real>::THREADS) void sweep_kernel(
 template <typename Real, bool NORM, bool SMALL>
 struct PointSweep {
     static constexpr bool F32 = sizeof(Real) == 4;
-    static constexpr int CELLS = NORM ? (F32 ? 256 : 512) : (SMALL ? 192 : 448);
+    static constexpr int CELLS = NORM ? (F32 ? 256 : 512) : (SMALL ? 192 : POINT_CELLS);
     static constexpr int THREADS = CELLS + 64;
 };
 
 template <typename Real, bool NORM, bool SMALL>
-__global__ __launch_bounds__((PointSweep<Real, NORM, SMALL>::THREADS)) void point_sweep_kernel(
-    Dims d, Coef cd, CStateT<Real> q, StateT<Real> qn, double* partials)
+__device__ __forceinline__ void point_sweep(const Dims& d, const CoefR<Real>& c, const CStateT<Real>& q,
+                                            const StateT<Real>& qn, int blk, double* partials)
 {
     constexpr int CELLS = PointSweep<Real, NORM, SMALL>::CELLS;
     __shared__ Real pc;
     __shared__ double red[NORM ? CELLS / 64 : 1][NF];
-    const CoefR<Real> c = coef_as<Real>(cd);
-    const int blk = xcd_block(blockIdx.x, gridDim.x), tid = threadIdx.x;
+    const int tid = threadIdx.x;
     const int n = d.ni * d.nj * d.nk;
     // the last wavefront's cells: 64 consecutive ones with the centre among them
     const bool extra = tid >= CELLS;
@@ -240,6 +239,13 @@ __global__ __launch_bounds__((PointSweep<Real, NORM, SMALL>::THREADS)) void poin
             partials[(size_t)blk * NF + tid] = t;
         }
     }
+}
+
+template <typename Real, bool NORM, bool SMALL>
+__global__ __launch_bounds__((PointSweep<Real, NORM, SMALL>::THREADS)) void point_sweep_kernel(
+    Dims d, Coef cd, CStateT<Real> q, StateT<Real> qn, double* partials)
+{
+    point_sweep<Real, NORM, SMALL>(d, coef_as<Real>(cd), q, qn, xcd_block(blockIdx.x, gridDim.x), partials);
 }
 
 // The step sweep's memory streams without its work: the same tiles, block
@@ -707,6 +713,49 @@ template hipError_t launch_batch<double>(const BatchCav*, const int*, const Batc
                                          hipStream_t);
 template hipError_t launch_batch<float>(const BatchCav*, const int*, const BatchItem*, int, bool, int, int,
                                         hipStream_t);
+
+// The batch's step with one cell per thread (as for a small grid, and bound
+// alike): every block is POINT_CELLS cells of one member, so no lanes idle at
+// ragged extents and no unit waits for a column to end.  A block finds its
+// member among the first blocks of all of them, 64 at a time (one load's
+// latency up to 64 members; a list of items would be one more).  8 FP64
+// members of 0.75 M cells together: 48 -> 25 us a step.
+template <typename Real>
+__global__ __launch_bounds__((PointSweep<Real, false, false>::THREADS)) void batch_point_kernel(
+    const BatchCav* __restrict__ cavs, int members, int parity)
+{
+    const int blk = xcd_block(blockIdx.x, gridDim.x), lane = threadIdx.x & 63;
+    int lo = 0;
+    for (int span = members; span > 1;) {
+        const int step = (span + 63) >> 6, m = lo + lane * step;
+        const bool at_or_before = lane * step < span && cavs[min(m, members - 1)].pstart <= blk;
+        const int at = (__popcll(__ballot(at_or_before)) - 1) * step;
+        lo += at;
+        span = min(step, span - at);
+    }
+    const BatchCav& cv = cavs[__builtin_amdgcn_readfirstlane(lo)];
+    const Dims d = cv.d;
+    const Real* cur = static_cast<const Real*>(parity ? cv.q_tmp : cv.q);
+    Real* nxt = static_cast<Real*>(parity ? cv.q : cv.q_tmp);
+    CStateT<Real> qs;
+    StateT<Real> qn;
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+        qs.f[f] = cur + f * cv.fstride;
+        qn.f[f] = nxt + f * cv.fstride;
+    }
+    point_sweep<Real, false, false>(d, coef_as<Real>(cv.c), qs, qn, blk - cv.pstart, nullptr);
+}
+
+template <typename Real>
+hipError_t launch_batch_points(const BatchCav* cavs, int members, int points, int parity, hipStream_t s)
+{
+    static_assert(PointSweep<Real, false, false>::CELLS == POINT_CELLS, "the table's blocks are the kernel's");
+    batch_point_kernel<Real><<<points, PointSweep<Real, false, false>::THREADS, 0, s>>>(cavs, members, parity);
+    return hipGetLastError();
+}
+template hipError_t launch_batch_points<double>(const BatchCav*, int, int, int, hipStream_t);
+template hipError_t launch_batch_points<float>(const BatchCav*, int, int, int, hipStream_t);
 
 // Residual norms from per-block partials: fixed-order sums (each thread its
 // strided blocks in order, all fields of a block at once so that its loads
