@@ -337,13 +337,14 @@ int open_kc(int32_t n, const cav_batch_member* members, double* planes = nullptr
 // where every member leaves its tile and chunk open and, by both launches'
 // measured cost in us, that one is cheaper.  planes: the tiles' cost in
 // planes (open_kc).  FP64: 5 + 27 a million cells (36 where both states of
-// all members exceed the 256 MB memory-side cache) against 2.3 a plane: 8
-// ragged members of 0.75 M cells together 25 against 48 us, 5 of 2.6 M 78
-// against 109, 40 of 4.6 M 175 against 228, 60 of 10 M 369 against 423; 60
+// all members exceed the memory-side cache) against 1.8 (2.3) a plane: 8
+// ragged members of 0.75 M cells together 25 against 44 us, 5 of 2.6 M 78
+// against 99, 40 of 4.6 M 175 against 228, 60 of 10 M 369 against 423; 60
 // cubes of 18 M, which fill their tiles, 616 against 530.  FP32: 4 + 14 (18
-// where the states exceed 150 MB) against 3.5 + 0.5 a plane: 3 members of 0.2 M
-// 7.0 against 9.1, 8 of 1.8 M 27 against 32, 16 of 2.4 M 37 against 43, 30 of
-// 4.4 M 72 against 71, 60 of 7.3 M 156 against 113.  (A member's cells and offsets: as in step_geom.)
+// where the states exceed 150 MB) against 3 + 0.44 a plane: 3 members of 0.2 M
+// 7.0 against 9.0, 8 of 1.0 M 17 against 22, 8 of 1.8 M 27 against 28, 16 of
+// 2.4 M 37 against 36, 30 of 4.4 M 72 against 64.  (A member's cells and
+// offsets: as in step_geom.)
 bool batch_points(int32_t n, const cav_batch_member* members, double planes)
 {
     const bool f32 = members[0].grid.dtype == CAV_F32;
@@ -355,8 +356,8 @@ bool batch_points(int32_t n, const cav_batch_member* members, double planes)
         cells += c;
     }
     const bool cached = cells * 2 * NF * (f32 ? 4 : 8) <= (f32 ? 150e6 : 250e6);
-    return f32 ? 4 + (cached ? 14e-6 : 18e-6) * cells < 3.5 + 0.5 * planes
-               : 5 + (cached ? 27e-6 : 36e-6) * cells < 2.3 * planes;
+    return f32 ? 4 + (cached ? 14e-6 : 18e-6) * cells < 3 + 0.44 * planes
+               : 5 + (cached ? 27e-6 : 36e-6) * cells < (cached ? 1.8 : 2.3) * planes;
 }
 
 int check_member(const cav_batch_member& m, int idx, int dtype)
@@ -391,7 +392,8 @@ hipError_t batch_launches(const cav_batch& b, int32_t nsteps, int nblocks, int p
         const bool last = n == nsteps - 1;
         auto go = [&] {
             return b.points && !last ? launch_batch_points<Real>(cavs, b.members, b.points, parity, stream)
-                                     : launch_batch<Real>(cavs, segs, items, parity, last, nblocks, b.shapes, stream);
+                                     : launch_batch<Real>(cavs, segs, items, parity, last, nblocks, b.shapes,
+                                                  stream_out<Real>((double)b.cells), stream);
         };
         e = timed ? run(last ? "batch_norm" : "batch", stream, go) : go();
         parity ^= 1;
@@ -478,15 +480,16 @@ int step_impl(const cav_grid* grid, const cav_params* prm, const cav_halo* halo,
         cur = nxt;
         nxt = t;
     }
-    if (norms) {
-        const double ncell = (double)d.ni * d.nj * d.nk;
+    const double ncell = (double)d.ni * d.nj * d.nk;
+    if (cur != q) {
+        e = go("copy", [&] {
+            return launch_copy_back<Real>(d, (long long)field_elems(d), static_cast<const Real*>(cur),
+                                          static_cast<Real*>(q), g.stream, partials, g.npart, ncell, norms, stream);
+        });
+        if (e != hipSuccess) return hip_fail("state copy", e);
+    } else if (norms) {
         e = go("norm_finalize", [&] { return launch_norm_finalize(partials, g.npart, ncell, norms, stream); });
         if (e != hipSuccess) return hip_fail("norm finalize launch", e);
-    }
-    if (cur != q) {
-        const size_t bytes = (size_t)NF * field_elems(d) * sizeof(Real);
-        e = go("copy", [&] { return hipMemcpyAsync(q, cur, bytes, hipMemcpyDeviceToDevice, stream); });
-        if (e != hipSuccess) return hip_fail("state copy", e);
     }
     return CAV_OK;
 }
@@ -578,7 +581,8 @@ int overlap_impl(const cav_grid* grid, const cav_params* prm, const HaloGeom& hg
     const Dims d = dims_of(grid);
     const Coef c = coef_of(grid, prm);
     const SweepGeom gi = tile_geom<Real>(d, device_slots());   // interior: the step sweep's tile
-    const SweepGeom g = sweep_geom(d, device_slots());          // exterior slabs: the 64 x 8 tiling
+    SweepGeom g = sweep_geom(d, device_slots());                // exterior slabs: the 64 x 8 tiling
+    g.stream = gi.stream;
     SplitGeom sg;
     if ((rc = split_geom(grid, hg, gi, g, ws_bytes, &sg))) return rc;
     const int nb_ext = exterior_blocks(d, g, sg);
@@ -620,13 +624,17 @@ int overlap_impl(const cav_grid* grid, const cav_params* prm, const HaloGeom& hg
         std::swap(cur, nxt);
     }
     const double ncell = (double)d.ni * d.nj * d.nk;
-    e = run("norm_finalize", stream,
-            [&] { return launch_norm_finalize(partials, gi.nblocks + nb_ext, ncell, wsd, stream); });
-    if (e != hipSuccess) return done(hip_fail("norm finalize launch", e));
     if (cur != q) {
-        const size_t bytes = (size_t)NF * field_elems(d) * sizeof(Real);
-        e = run("copy", stream, [&] { return hipMemcpyAsync(q, cur, bytes, hipMemcpyDeviceToDevice, stream); });
+        e = run("copy", stream, [&] {
+            return launch_copy_back<Real>(d, (long long)field_elems(d), static_cast<const Real*>(cur),
+                                          static_cast<Real*>(q), g.stream, partials, gi.nblocks + nb_ext, ncell, wsd,
+                                          stream);
+        });
         if (e != hipSuccess) return done(hip_fail("state copy", e));
+    } else {
+        e = run("norm_finalize", stream,
+                [&] { return launch_norm_finalize(partials, gi.nblocks + nb_ext, ncell, wsd, stream); });
+        if (e != hipSuccess) return done(hip_fail("norm finalize launch", e));
     }
     return done(CAV_OK);
 }

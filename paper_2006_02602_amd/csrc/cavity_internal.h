@@ -72,7 +72,24 @@ struct SweepGeom {
     int nblocks;              // tiles_i * tiles_j * nkc
     bool point, point_norm;   // the step without / with norms runs one cell per thread
     int npart;                // norm partials of the step with norms
+    bool stream;              // the step's new state leaves by non-temporal stores
 };
+// Whether the tiles' new states (cells in all) go out by non-temporal stores:
+// where both states together exceed the 256 MB memory-side cache, so that the
+// next step finds nothing of them there (FP64 152^3, 281 MB: 69.6 us a step
+// against 73.7 by plain stores, 256^3 248 against 258; FP32 192^3 73 against
+// 77), and where the L2s hold both (32 MB), whose dirty lines the launch would
+// have to write back at its end (FP64 64^3: 8.5 against 9.0, 72^3, 30 MB, 14.6
+// against 14.9).  Between them plain stores leave the state in the caches:
+// FP64 80^3 16.1 against 17.7, 128^3 30.5 against 39.6, 144^3, 239 MB, 60.2
+// against 62.1; FP32 96^3 10.7 against 12.9, 160^3 32.6 against 43.5, 176^3,
+// 218 MB, 51 against 61.
+template <typename Real>
+inline bool stream_out(double cells)
+{
+    const double bytes = cells * 2 * NF * sizeof(Real);
+    return bytes <= 32e6 || bytes >= 256e6;
+}
 // ti x tj: the tile of the launch; per_cu: its blocks resident at once per
 // compute unit; streams_f64: an FP64 launch that moves the state at the
 // memory's pace (the step), not its blocks' own
@@ -161,6 +178,11 @@ hipError_t launch_sweep(const Dims& d, const Coef& c, const SweepGeom& g, CState
                         Real* xbuf = nullptr, bool xpack = false);
 hipError_t launch_norm_finalize(const double* partials, int nblocks, double ncell, double* out,
                                 hipStream_t s);
+// Interior cells src -> dst (fs elements a field); out not NULL: with
+// launch_norm_finalize's work.
+template <typename Real>
+hipError_t launch_copy_back(const Dims& d, long long fs, const Real* src, Real* dst, bool stream, const double* partials,
+                            int nblocks, double ncell, double* out, hipStream_t s);
 hipError_t launch_math(const double* x, double* out, int n, hipStream_t s);
 // g comes from step_geom<Real>
 template <typename Real>
@@ -171,7 +193,7 @@ hipError_t launch_halo(const Dims& d, const HaloGeom& h, StateT<Real> q, Real* b
 template <typename Real>
 // shapes: the tile shapes among the members (1 wide, 2 narrow, 3 both)
 hipError_t launch_batch(const BatchCav* cavs, const int* segs, const BatchItem* items, int parity, bool with_norm,
-                        int nblocks, int shapes, hipStream_t s);
+                        int nblocks, int shapes, bool stream, hipStream_t s);
 hipError_t launch_batch_norms(const BatchCav* cavs, int members, hipStream_t s);
 // The step of a batch (without norms) with one cell per thread: points blocks,
 // POINT_CELLS cells of one member each.

@@ -105,8 +105,8 @@ struct ExchangedColumn {
 };
 
 // The pack, in the step's epilogue.
-template <typename Real>
-struct StepXPackEpi : StepEpi<Real> {
+template <typename Real, bool STREAM>
+struct StepXPackEpi : StepEpi<Real, STREAM> {
     Real* buf;
     XColumn c;
     XGeom x;
@@ -115,8 +115,7 @@ struct StepXPackEpi : StepEpi<Real> {
     {
         const Real nv[NF] = {fma(dt, R[FP], s.p) - this->pc_new, fma(dt, R[FU], s.u), fma(dt, R[FV], s.v),
                              fma(dt, R[FW], s.w), fma(dt, R[FT], s.t)};
-#pragma unroll
-        for (int f = 0; f < NF; ++f) __builtin_nontemporal_store(nv[f], &this->qn.f[f][o]);
+        this->store(nv, o);
 #pragma unroll
         for (int f = 0; f < NF; ++f) acc[f] = fma((double)R[f], (double)R[f], acc[f]);
         if (c.dd < 0) return;
@@ -130,7 +129,7 @@ struct StepXPackEpi : StepEpi<Real> {
 // need no field loads (the kernel the uniform-wall problem runs).  X: 1 the
 // exchange's unpack in the loads, 2 also the next one's pack in the epilogue
 // (buffer xbuf, geometry xg).
-template <typename Real, bool NORM, bool FIELD, int X>
+template <typename Real, bool NORM, bool FIELD, int X, bool STREAM>
 __global__ __launch_bounds__(StepTile<Real>::THREADS) void sweep_kernel(
     Dims d, Coef cd, SweepGeom g, CStateT<Real> q, StateT<Real> qn, double* partials, XGeom xg, Real* xbuf)
 {
@@ -144,21 +143,21 @@ __global__ __launch_bounds__(StepTile<Real>::THREADS) void sweep_kernel(
         col.buf = xbuf;
         col.x = xg;
         if constexpr (X == 2) {
-            StepXPackEpi<Real> epi;
+            StepXPackEpi<Real, STREAM> epi;
             epi.qn = qn;
             epi.pc_new = Real(0);
             epi.x = xg;
             epi.buf = xbuf;
             const int tid = threadIdx.x + SW_TI * threadIdx.y;
             epi.c.init(xg, d, tb.i0 + tid % TI, tb.j0 + tid / TI);
-            sweep_tile<Real, NORM, OwnAll, StepXPackEpi<Real>, TI, TJ>(d, c, tb, OwnAll{}, q, epi, partials, L, col);
+            sweep_tile<Real, NORM, OwnAll, StepXPackEpi<Real, STREAM>, TI, TJ>(d, c, tb, OwnAll{}, q, epi, partials, L, col);
         } else {
-            StepEpi<Real> epi{qn, Real(0)};
-            sweep_tile<Real, NORM, OwnAll, StepEpi<Real>, TI, TJ>(d, c, tb, OwnAll{}, q, epi, partials, L, col);
+            StepEpi<Real, STREAM> epi{qn, Real(0)};
+            sweep_tile<Real, NORM, OwnAll, StepEpi<Real, STREAM>, TI, TJ>(d, c, tb, OwnAll{}, q, epi, partials, L, col);
         }
     } else {
-        StepEpi<Real> epi{qn, Real(0)};
-        sweep_tile<Real, NORM, OwnAll, StepEpi<Real>, TI, TJ>(d, c, tb, OwnAll{}, q, epi, partials, L);
+        StepEpi<Real, STREAM> epi{qn, Real(0)};
+        sweep_tile<Real, NORM, OwnAll, StepEpi<Real, STREAM>, TI, TJ>(d, c, tb, OwnAll{}, q, epi, partials, L);
     }
 }
 
@@ -323,14 +322,15 @@ SweepGeom sweep_geom(const Dims& d, int cus, int ti, int tj, int per_cu, bool st
     // earliest: blocks run in rounds of `slots` (the blocks resident at
     // once), a block costs its planes plus ~3 planes of start-up (the queue
     // and halo planes it loads before its first plane).  An FP64 sweep whose
-    // two states exceed the memory-side cache is bound by HBM, which four
-    // fifths of the blocks keep busy: there the planes of all blocks count,
+    // two states exceed the 256 MB memory-side cache is bound by HBM, which
+    // four fifths of the blocks keep busy: there the planes of all blocks count,
     // until the rounds at that rate take longer (192^3: 3 chunks 117 us, the 7
-    // that minimise the rounds 123; 224^3 187 against 202; 144x150x160 71
-    // against 70).  In FP32, with three blocks per CU, the rule does harm
-    // (176^3 68 against 62 us, 224^3 121 against 109; 256^3 142 against 152).
+    // that minimise the rounds 123; 224^3 187 against 202).  Below that size
+    // the rule does harm (136^3 54 against 44 us, 140x140x150 78 against 65),
+    // and in FP32, with three blocks per CU (176^3 68 against 62 us, 224^3 121
+    // against 109; 256^3 142 against 152).
     const int overhead = 3;
-    const bool hbm = streams_f64 && 2.0 * NF * sizeof(double) * d.ni * d.nj * d.nk > 192e6;
+    const bool hbm = streams_f64 && 2.0 * NF * sizeof(double) * d.ni * d.nj * d.nk > 256e6;
     double best_cost = -1.0;
     int best = 1;
     const int max_nkc = max(1, d.nk / CAV_MIN_KC);
@@ -348,7 +348,7 @@ SweepGeom sweep_geom(const Dims& d, int cus, int ti, int tj, int per_cu, bool st
     g.kc = (d.nk + best - 1) / best;
     g.nkc = (d.nk + g.kc - 1) / g.kc;
     g.nblocks = tiles * g.nkc;
-    g.point = g.point_norm = false;
+    g.point = g.point_norm = g.stream = false;
     g.npart = g.nblocks;
     return g;
 }
@@ -361,24 +361,26 @@ SweepGeom tile_geom(const Dims& d, int cus)
     static int per_cu = 0;
     if (per_cu == 0) {
         int n = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sweep_kernel<Real, false, false, 0>,
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sweep_kernel<Real, false, false, 0, true>,
                                                          StepTile<Real>::THREADS, 0) != hipSuccess ||
             n < 1)
             n = 1;
         per_cu = n;
     }
-    return sweep_geom(d, cus, StepTile<Real>::TI, StepTile<Real>::TJ, per_cu, sizeof(Real) == 8);
+    SweepGeom g = sweep_geom(d, cus, StepTile<Real>::TI, StepTile<Real>::TJ, per_cu, sizeof(Real) == 8);
+    g.stream = stream_out<Real>((double)d.ni * d.nj * d.nk);
+    return g;
 }
 template SweepGeom tile_geom<double>(const Dims&, int);
 template SweepGeom tile_geom<float>(const Dims&, int);
 
-// The tile, or one cell per thread where that is faster.  FP32: while both
-// states stay in the 256 MB memory-side cache (160^3, 164 MB: 39 against 44
-// us; 176^3, 218 MB: 59-66 against 62 us).  FP64: by both kernels' measured
-// cost in us: the tile 4.9 + 1.65 a plane of its blocks (48^3 8.2, 72^3 14.7,
-// 96^3 22.1, 161x97x130 42.2, 144x150x160 71), the other 4 + 21 per million
-// cells (5.9, 12.7, 21.4, 45.6, 101); they cross twice, near 56^3, where the
-// tile's chunks reach their shortest, and near 90^3.  (A grid of 4.2 million
+// The tile, or one cell per thread where that is faster.  FP32: up to a
+// million cells (96^3: 10.3 against 10.7 us; 112^3 16.2 against 15.2, 128^3
+// 20.4 against 18.2, 131x67x201 23.0 against 19.1).  FP64: by both kernels'
+// measured cost in us: the tile 4.9 + 1.55 a plane of its blocks (48^3 8.3,
+// 72^3 14.6, 80^3 16.1, 96^3 20.6, 128^3 30.5), the other 4.5 + 20 per million
+// cells (6.2, 12.7, 14.9, 21.4, 45.6); they cross twice, near 56^3, where the
+// tile's chunks reach their shortest, and near 88^3.  (A grid of 4.2 million
 // cells has at most 48 (FP64) or 96 (FP32) padded elements a cell, so that
 // kernel's byte offsets fit in 32 bits.)  With norms only up to 150 thousand
 // cells: each wavefront's five butterflies cost as much as its residual
@@ -391,8 +393,8 @@ SweepGeom step_geom(const Dims& d, int cus)
     const long long n = (long long)d.ni * d.nj * d.nk;
     constexpr int CELLS = PointSweep<Real, true, false>::CELLS;
     const int rounds = (g.nblocks + cus - 1) / cus;
-    g.point = sizeof(Real) == 4 ? n <= 4200000
-                                : n <= 4200000 && 4.0 + 21e-6 * (double)n < 4.9 + 1.65 * rounds * g.kc;
+    g.point = sizeof(Real) == 4 ? n <= 1000000
+                                : n <= 4200000 && 4.5 + 20e-6 * (double)n < 4.9 + 1.55 * rounds * g.kc;
     g.point_norm = g.point && n <= 150000;
     if (g.point_norm) g.npart = (int)((n + CELLS - 1) / CELLS);
     return g;
@@ -434,16 +436,20 @@ hipError_t launch_sweep(const Dims& d, const Coef& c, const SweepGeom& g, CState
             xg.wpre[f] = xh->wpre[f];
         }
     }
-    auto go = [&](auto field) {
-        constexpr bool F = decltype(field)::value;
-        if (with_norm && xh) sweep_kernel<Real, true, F, 1><<<grid, block, 0, s>>>(d, c, g, q, qn, partials, xg, xbuf);
-        else if (with_norm) sweep_kernel<Real, true, F, 0><<<grid, block, 0, s>>>(d, c, g, q, qn, partials, xg, xbuf);
-        else if (xh && xpack) sweep_kernel<Real, false, F, 2><<<grid, block, 0, s>>>(d, c, g, q, qn, partials, xg, xbuf);
-        else if (xh) sweep_kernel<Real, false, F, 1><<<grid, block, 0, s>>>(d, c, g, q, qn, partials, xg, xbuf);
-        else sweep_kernel<Real, false, F, 0><<<grid, block, 0, s>>>(d, c, g, q, qn, partials, xg, xbuf);
+    auto go = [&](auto field, auto stream) {
+        constexpr bool F = decltype(field)::value, S = decltype(stream)::value;
+        if (with_norm && xh) sweep_kernel<Real, true, F, 1, S><<<grid, block, 0, s>>>(d, c, g, q, qn, partials, xg, xbuf);
+        else if (with_norm) sweep_kernel<Real, true, F, 0, S><<<grid, block, 0, s>>>(d, c, g, q, qn, partials, xg, xbuf);
+        else if (xh && xpack) sweep_kernel<Real, false, F, 2, S><<<grid, block, 0, s>>>(d, c, g, q, qn, partials, xg, xbuf);
+        else if (xh) sweep_kernel<Real, false, F, 1, S><<<grid, block, 0, s>>>(d, c, g, q, qn, partials, xg, xbuf);
+        else sweep_kernel<Real, false, F, 0, S><<<grid, block, 0, s>>>(d, c, g, q, qn, partials, xg, xbuf);
     };
-    if (c.t_hot_field) go(std::true_type{});
-    else go(std::false_type{});
+    auto pick = [&](auto stream) {
+        if (c.t_hot_field) go(std::true_type{}, stream);
+        else go(std::false_type{}, stream);
+    };
+    if (g.stream) pick(std::true_type{});
+    else pick(std::false_type{});
     return hipGetLastError();
 }
 template hipError_t launch_sweep<double>(const Dims&, const Coef&, const SweepGeom&, CStateT<double>,
@@ -501,7 +507,7 @@ struct OwnSlab {
 
 // The interior launch runs the step sweep's tile of its type (g from
 // step_geom<Real>).
-template <typename Real, bool NORM, bool FIELD>
+template <typename Real, bool NORM, bool FIELD, bool STREAM>
 __global__ __launch_bounds__(StepTile<Real>::THREADS) void interior_kernel(Dims d, Coef cd, SweepGeom g, SplitGeom sg,
                                                                            CStateT<Real> q, StateT<Real> qn,
                                                                            double* partials, int)
@@ -511,8 +517,8 @@ __global__ __launch_bounds__(StepTile<Real>::THREADS) void interior_kernel(Dims 
     CoefR<Real> c = coef_as<Real>(cd);
     if constexpr (!FIELD) c.t_hot_field = nullptr;
     const TileBox tb = tile_box<TI, TJ>(d, g.tiles_i, g.tiles_j, g.kc, xcd_block(blockIdx.x, g.nblocks));
-    StepEpi<Real> epi{qn, Real(0)};
-    sweep_tile<Real, NORM, OwnInterior, StepEpi<Real>, TI, TJ>(d, c, tb, OwnInterior{sg}, q,
+    StepEpi<Real, STREAM> epi{qn, Real(0)};
+    sweep_tile<Real, NORM, OwnInterior, StepEpi<Real, STREAM>, TI, TJ>(d, c, tb, OwnInterior{sg}, q,
                                                                                      epi, partials, L);
 }
 
@@ -522,7 +528,7 @@ __global__ __launch_bounds__(StepTile<Real>::THREADS) void interior_kernel(Dims 
 // cut).
 // Norm partials follow the interior launch's, at pidx = pidx0 + b (pidx0:
 // the interior launch's block count).  g: the 64 x 8 tiling (sweep_geom).
-template <typename Real, bool NORM, bool FIELD>
+template <typename Real, bool NORM, bool FIELD, bool STREAM>
 __global__ __launch_bounds__(SW_TI * SW_TJ) void exterior_kernel(Dims d, Coef cd, SweepGeom g, SplitGeom sg,
                                                                  CStateT<Real> q, StateT<Real> qn,
                                                                  double* partials, int pidx0)
@@ -566,9 +572,9 @@ __global__ __launch_bounds__(SW_TI * SW_TJ) void exterior_kernel(Dims d, Coef cd
         tb.k1 = cut + sg.m;
     }
     tb.pidx = pidx0 + b;
-    StepEpi<Real> epi{qn, Real(0)};
+    StepEpi<Real, STREAM> epi{qn, Real(0)};
     if (axis == 0)          // 2m <= 8 owned columns: a narrow tile wastes fewer lanes
-        sweep_tile<Real, NORM, OwnSlab, StepEpi<Real>, XS_TI, XS_TJ>(d, c, tb, OwnSlab{sg, axis, cut}, q, epi,
+        sweep_tile<Real, NORM, OwnSlab, StepEpi<Real, STREAM>, XS_TI, XS_TJ>(d, c, tb, OwnSlab{sg, axis, cut}, q, epi,
                                                                       partials, L.x);
     else
         sweep_tile<Real, NORM>(d, c, tb, OwnSlab{sg, axis, cut}, q, epi, partials, L.yz);
@@ -594,20 +600,23 @@ hipError_t launch_split(const Dims& d, const Coef& c, const SweepGeom& gi, const
     const int pidx0 = gi.nblocks;
     if (nb == 0) return hipSuccess;
     const bool fld = c.t_hot_field != nullptr;
-#define SPLIT_LAUNCH(K)                                                                                       \
+#define SPLIT_LAUNCH(K, S)                                                                                    \
     do {                                                                                                      \
         if (fld) {                                                                                            \
-            if (with_norm) K<Real, true, true><<<nb, block, 0, s>>>(d, c, gl, sg, q, qn, partials, pidx0);     \
-            else K<Real, false, true><<<nb, block, 0, s>>>(d, c, gl, sg, q, qn, partials, pidx0);              \
+            if (with_norm) K<Real, true, true, S><<<nb, block, 0, s>>>(d, c, gl, sg, q, qn, partials, pidx0);  \
+            else K<Real, false, true, S><<<nb, block, 0, s>>>(d, c, gl, sg, q, qn, partials, pidx0);           \
         } else {                                                                                              \
-            if (with_norm) K<Real, true, false><<<nb, block, 0, s>>>(d, c, gl, sg, q, qn, partials, pidx0);    \
-            else K<Real, false, false><<<nb, block, 0, s>>>(d, c, gl, sg, q, qn, partials, pidx0);             \
+            if (with_norm) K<Real, true, false, S><<<nb, block, 0, s>>>(d, c, gl, sg, q, qn, partials, pidx0); \
+            else K<Real, false, false, S><<<nb, block, 0, s>>>(d, c, gl, sg, q, qn, partials, pidx0);          \
         }                                                                                                     \
     } while (0)
-    if (exterior)
-        SPLIT_LAUNCH(exterior_kernel);
-    else
-        SPLIT_LAUNCH(interior_kernel);
+    if (exterior) {
+        if (gl.stream) SPLIT_LAUNCH(exterior_kernel, true);
+        else SPLIT_LAUNCH(exterior_kernel, false);
+    } else {
+        if (gl.stream) SPLIT_LAUNCH(interior_kernel, true);
+        else SPLIT_LAUNCH(interior_kernel, false);
+    }
 #undef SPLIT_LAUNCH
     return hipGetLastError();
 }
@@ -654,7 +663,7 @@ __device__ __forceinline__ void for_each_item(const int* __restrict__ segs, F&& 
 // SHAPES: 3 = each member's tile shape (both compiled in: the registers of
 // the larger, two blocks per CU in FP32), 1 = the wide shape only, 2 = the
 // narrow one only (one shape: three blocks per CU in FP32).
-template <typename Real, bool NORM, int SHAPES>
+template <typename Real, bool NORM, int SHAPES, bool STREAM>
 __global__ __launch_bounds__(BatchTiles<Real>::THREADS, SHAPES == 3 ? 0 : BatchTiles<Real>::MINW1) void batch_kernel(
     const BatchCav* __restrict__ cavs, const int* __restrict__ segs, const BatchItem* __restrict__ items, int parity)
 {
@@ -679,14 +688,14 @@ __global__ __launch_bounds__(BatchTiles<Real>::THREADS, SHAPES == 3 ? 0 : BatchT
             qs.f[f] = cur + f * cv.fstride;
             qn.f[f] = nxt + f * cv.fstride;
         }
-        StepEpi<Real> epi{qn, Real(0)};
+        StepEpi<Real, STREAM> epi{qn, Real(0)};
         if (SHAPES == 2 || (SHAPES == 3 && cv.ti == BT::NTI)) {
             const TileBox tb = tile_box<BT::NTI, BT::NTJ>(d, cv.tiles_i, cv.tiles_j, cv.kc, w.tile);
-            sweep_tile<Real, NORM, OwnAll, StepEpi<Real>, BT::NTI, BT::NTJ>(
+            sweep_tile<Real, NORM, OwnAll, StepEpi<Real, STREAM>, BT::NTI, BT::NTJ>(
                 d, c, tb, OwnAll{}, qs, epi, cv.ws + WS_HEAD_DOUBLES, L.narrow);
         } else {
             const TileBox tb = tile_box<BT::WTI, BT::WTJ>(d, cv.tiles_i, cv.tiles_j, cv.kc, w.tile);
-            sweep_tile<Real, NORM, OwnAll, StepEpi<Real>, BT::WTI, BT::WTJ>(
+            sweep_tile<Real, NORM, OwnAll, StepEpi<Real, STREAM>, BT::WTI, BT::WTJ>(
                 d, c, tb, OwnAll{}, qs, epi, cv.ws + WS_HEAD_DOUBLES, L.wide);
         }
         __syncthreads();                  // LDS is reused by the next item
@@ -695,13 +704,15 @@ __global__ __launch_bounds__(BatchTiles<Real>::THREADS, SHAPES == 3 ? 0 : BatchT
 
 template <typename Real>
 hipError_t launch_batch(const BatchCav* cavs, const int* segs, const BatchItem* items, int parity, bool with_norm,
-                        int nblocks, int shapes, hipStream_t s)
+                        int nblocks, int shapes, bool stream, hipStream_t s)
 {
     dim3 block(SW_TI, BatchTiles<Real>::THREADS / SW_TI), grid(nblocks);
-#define BATCH_LAUNCH(SH)                                                                      \
-    do {                                                                                      \
-        if (with_norm) batch_kernel<Real, true, SH><<<grid, block, 0, s>>>(cavs, segs, items, parity);  \
-        else batch_kernel<Real, false, SH><<<grid, block, 0, s>>>(cavs, segs, items, parity);           \
+#define BATCH_LAUNCH(SH)                                                                                \
+    do {                                                                                                \
+        if (with_norm && stream) batch_kernel<Real, true, SH, true><<<grid, block, 0, s>>>(cavs, segs, items, parity);  \
+        else if (with_norm) batch_kernel<Real, true, SH, false><<<grid, block, 0, s>>>(cavs, segs, items, parity);      \
+        else if (stream) batch_kernel<Real, false, SH, true><<<grid, block, 0, s>>>(cavs, segs, items, parity);         \
+        else batch_kernel<Real, false, SH, false><<<grid, block, 0, s>>>(cavs, segs, items, parity);                    \
     } while (0)
     if (shapes == 1) BATCH_LAUNCH(1);
     else if (shapes == 2) BATCH_LAUNCH(2);
@@ -710,9 +721,9 @@ hipError_t launch_batch(const BatchCav* cavs, const int* segs, const BatchItem* 
     return hipGetLastError();
 }
 template hipError_t launch_batch<double>(const BatchCav*, const int*, const BatchItem*, int, bool, int, int,
-                                         hipStream_t);
+                                         bool, hipStream_t);
 template hipError_t launch_batch<float>(const BatchCav*, const int*, const BatchItem*, int, bool, int, int,
-                                        hipStream_t);
+                                        bool, hipStream_t);
 
 // The batch's step with one cell per thread (as for a small grid, and bound
 // alike): every block is POINT_CELLS cells of one member, so no lanes idle at
@@ -979,5 +990,83 @@ hipError_t launch_norm_finalize(const double* partials, int nblocks, double ncel
     norm_finalize_kernel<<<1, 1024, 0, s>>>(partials, nblocks, ncell, out);
     return hipGetLastError();
 }
+
+// The end of an odd number of steps: the interior cells of src copied to dst,
+// VE elements (16 bytes, or one element of an unaligned state) a lane, row by
+// row in whole 128-byte lines (a row's last one takes ghost and padding cells
+// along: part of a line costs more to write; 170^3 FP32 95 -> 90 us for one
+// step).  Bound by memory: COPY_CHUNKS chunks of a plane a block, four in
+// flight a lane.  With norms (out not NULL) the first block finalizes them
+// meanwhile, in norm_finalize_kernel's order.  STREAM: as the sweep's stores;
+// the loads too, which otherwise leave src cached for the next step to write
+// (161x97x130: 76 -> 67 us).  One step with its norms, by a copy of the whole
+// array after the norms against this: FP64 64^3 24.5 -> 20, 128^3 74 -> 59,
+// 256^3 554 -> 473; FP32 64^3 19.7 -> 14.7, 256^3 325 -> 270.
+constexpr int COPY_THREADS = 1024, COPY_UNROLL = 4, COPY_CHUNKS = COPY_THREADS * COPY_UNROLL;
+
+template <typename Real, bool STREAM, int VE>
+__global__ __launch_bounds__(COPY_THREADS) void copy_back_kernel(Dims d, long long fs, int bpp, const Real* __restrict__ src,
+                                                                 Real* __restrict__ dst, const double* part, int nb,
+                                                                 double ncell, double* out)
+{
+    typedef Real Vec __attribute__((ext_vector_type(VE)));
+    int blk = blockIdx.x;
+    if (out) {
+        if (blk == 0) {
+            finalize_norms<COPY_THREADS>(part, nb, ncell, out);
+            return;
+        }
+        --blk;
+    }
+    const int plane = blk / bpp, seg = blk - plane * bpp;
+    const int f = plane / d.nk, k = plane - f * d.nk;
+    const long long base = f * fs + cell_off(d, 0, 0, k);
+    constexpr int LINE = ROW_ALIGN_BYTES / sizeof(Real);
+    const int cpr = (d.ni + LINE - 1) / LINE * (LINE / VE), n = d.nj * cpr;
+    const int t0 = seg * COPY_CHUNKS + threadIdx.x;
+    Vec v[COPY_UNROLL];
+    int o[COPY_UNROLL];
+#pragma unroll
+    for (int r = 0; r < COPY_UNROLL; ++r) {
+        const int t = min(t0 + r * COPY_THREADS, n - 1), row = t / cpr;
+        o[r] = row * d.sy + (t - row * cpr) * VE;
+        const Vec* a = reinterpret_cast<const Vec*>(src + base + o[r]);
+        v[r] = STREAM ? __builtin_nontemporal_load(a) : *a;
+    }
+#pragma unroll
+    for (int r = 0; r < COPY_UNROLL; ++r) {
+        if (t0 + r * COPY_THREADS >= n) break;
+        if (STREAM) __builtin_nontemporal_store(v[r], reinterpret_cast<Vec*>(dst + base + o[r]));
+        else *reinterpret_cast<Vec*>(dst + base + o[r]) = v[r];
+    }
+}
+
+template <typename Real>
+hipError_t launch_copy_back(const Dims& d, long long fs, const Real* src, Real* dst, bool stream, const double* partials,
+                            int nblocks, double ncell, double* out, hipStream_t s)
+{
+    auto go = [&](auto str, auto width) {
+        constexpr int VE = decltype(width)::value;
+        constexpr int LINE = ROW_ALIGN_BYTES / sizeof(Real);
+        const int bpp = (d.nj * ((d.ni + LINE - 1) / LINE * (LINE / VE)) + COPY_CHUNKS - 1) / COPY_CHUNKS;
+        const int grid = NF * d.nk * bpp + (out ? 1 : 0);
+        copy_back_kernel<Real, decltype(str)::value, VE>
+            <<<grid, COPY_THREADS, 0, s>>>(d, fs, bpp, src, dst, partials, nblocks, ncell, out);
+    };
+    // rows are at multiples of 128 bytes of the state, which the caller may
+    // have aligned to one element only
+    const bool wide = (reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) % 16 == 0;
+    auto pick = [&](auto str) {
+        if (wide) go(str, std::integral_constant<int, 16 / sizeof(Real)>{});
+        else go(str, std::integral_constant<int, 1>{});
+    };
+    if (stream) pick(std::true_type{});
+    else pick(std::false_type{});
+    return hipGetLastError();
+}
+template hipError_t launch_copy_back<double>(const Dims&, long long, const double*, double*, bool, const double*, int,
+                                             double, double*, hipStream_t);
+template hipError_t launch_copy_back<float>(const Dims&, long long, const float*, float*, bool, const double*, int,
+                                            double, double*, hipStream_t);
 
 }  // namespace cav

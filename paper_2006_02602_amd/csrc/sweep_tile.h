@@ -37,10 +37,20 @@ struct SweepLds {
 // What a sweep does with each cell's stars and residual: the pseudo-time
 // update of Sec. 2 (q + dt R, then the centre rescale of p) streamed into
 // qn, and R^2 into the norm accumulators.
-template <typename Real>
+// STREAM: by non-temporal stores (stream_out; compiled in, since of the two
+// kinds of store under a condition the compiler makes one).
+template <typename Real, bool STREAM>
 struct StepEpi {
     StateT<Real> qn;
     Real pc_new;
+    __device__ __forceinline__ void store(const Real v[NF], int o)
+    {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            if (STREAM) __builtin_nontemporal_store(v[f], &qn.f[f][o]);
+            else qn.f[f][o] = v[f];
+        }
+    }
     // New pressure at the centre cell, recomputed with the same arithmetic
     // as its owner, so that every block subtracts the identical value.
     __device__ __forceinline__ void prepare(const Dims& d, const CStateT<Real>& q, const CoefR<Real>& c)
@@ -54,12 +64,9 @@ struct StepEpi {
     __device__ __forceinline__ void cell(const CoefR<Real>&, const Star<Real>& s, const Real R[NF], Real dt, int o,
                                          int, int, int, double acc[NF])
     {
-        // the new state is not read again by this launch: stream it out
-        __builtin_nontemporal_store(fma(dt, R[FP], s.p) - pc_new, &qn.f[FP][o]);
-        __builtin_nontemporal_store(fma(dt, R[FU], s.u), &qn.f[FU][o]);
-        __builtin_nontemporal_store(fma(dt, R[FV], s.v), &qn.f[FV][o]);
-        __builtin_nontemporal_store(fma(dt, R[FW], s.w), &qn.f[FW][o]);
-        __builtin_nontemporal_store(fma(dt, R[FT], s.t), &qn.f[FT][o]);
+        const Real v[NF] = {fma(dt, R[FP], s.p) - pc_new, fma(dt, R[FU], s.u), fma(dt, R[FV], s.v),
+                            fma(dt, R[FW], s.w), fma(dt, R[FT], s.t)};
+        store(v, o);
 #pragma unroll
         for (int f = 0; f < NF; ++f) acc[f] = fma((double)R[f], (double)R[f], acc[f]);
     }
