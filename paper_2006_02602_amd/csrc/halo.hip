@@ -22,6 +22,8 @@
 #include "cavity_internal.h"
 #include "halo_layout.h"
 
+#include <type_traits>
+
 namespace cav {
 
 template <typename Real>
@@ -193,17 +195,121 @@ __global__ __launch_bounds__(HALO_THREADS) void halo_kernel(Dims d, HaloGeom h, 
     if (MODE != HALO_PACK) put_state();
 }
 
+// The same with one field a thread, for small exchanges: those are bound by a
+// launch's start, of which the code fetched before the first load is a large
+// part, and by the few loads in flight (pack, us: 16^3 2x2x2 4.2 -> 3.3, 64^3
+// 6.7 -> 4.0, 96^3 6.9 -> 5.3; the exchange of a 16^3 step 6.2 -> 4.0).
+template <typename Real, HaloMode MODE>
+__global__ __launch_bounds__(HALO_THREADS) void halo_field_kernel(Dims d, HaloGeom h, long long fs,
+                                                                  Real* __restrict__ q,
+                                                                  Real* __restrict__ buf)
+{
+    using R2 = typename Pair<Real>::T;
+    // blocks of one axis: faces, then fields, then the face's cells
+    int blk = blockIdx.x;
+    const int axis = blk < h.blk_end[0] * NF ? 0 : (blk < h.blk_end[1] * NF ? 1 : 2);
+    if (axis > 0) blk -= h.blk_end[axis - 1] * NF;
+    const int r1 = blk >> 1, r2 = r1 / NF, f = r1 - r2 * NF;
+    const int pair = r2 / h.bpf[axis], fblk = r2 - pair * h.bpf[axis];
+    const int fidx = 2 * pair + (blk & 1);
+    const int w = h.w[f];
+    if (w == 0) return;
+    int a, b, c, face;
+    face_of(h, axis, fidx, a, b, c, face);
+    const bool high = face & 1;
+    const int area = (int)h.area[axis];
+    const int ex = h.e[0], ey = h.e[1], ez = h.e[2];
+
+    // the field's box in the buffer, and the state at the face's first layer
+    // at tangential cell 0
+    Real* const B = buf + (face_offset(h, a, b, c, face) * h.wsum + (long long)h.wpre[f] * area);
+    const int ci = axis == 0 && high ? (a + 1) * ex - w : a * ex;
+    const int cj = axis == 1 && high ? (b + 1) * ey - w : b * ey;
+    const int ck = axis == 2 && high ? (c + 1) * ez - w : c * ez;
+    Real* const Q = q + (f * fs + cell_off(d, ci, cj, ck));
+    // steps of the layers, and of the tangential cells (ta, tb): (j, k) on i
+    // faces, (i, k) on j faces, (i, j) on k faces; the box is in (k, j, i)
+    // order, i fastest
+    const int ne = axis == 0 ? ey : ex;
+    const int lq = axis == 0 ? 1 : (axis == 1 ? d.sy : d.sz), lb = axis == 0 ? 1 : (axis == 1 ? ex : area);
+    const int qa = axis == 0 ? d.sy : 1, qb = axis == 2 ? d.sy : d.sz;
+    const int ba = axis == 0 ? w : 1, bb = axis == 2 ? ex : ne * w;
+    // two layers of an i face move as one pair where the address allows
+    auto pairs = [&](const Real* p) { return axis == 0 && w == 2 && (reinterpret_cast<uintptr_t>(p) % sizeof(R2)) == 0; };
+    // rows of the state start at even elements and boxes hold pairs, so that
+    // one answer holds for all cells
+    const bool qpair = pairs(Q), bpair = pairs(B);
+
+    int oq[HALO_ROWS], ob[HALO_ROWS];
+    bool ok[HALO_ROWS];
+    Real v[HALO_ROWS][2];
+#pragma unroll
+    for (int r = 0; r < HALO_ROWS; ++r) {
+        const int t = fblk * (HALO_THREADS * HALO_ROWS) + r * HALO_THREADS + threadIdx.x;
+        ok[r] = t < area;
+        const int tb = t / ne, ta = t - tb * ne;
+        oq[r] = ok[r] ? tb * qb + ta * qa : 0;
+        ob[r] = ok[r] ? tb * bb + ta * ba : 0;
+    }
+    auto get = [&](const Real* P, const int* o, int l, bool pair) __attribute__((always_inline)) {
+        if (pair) {
+#pragma unroll
+            for (int r = 0; r < HALO_ROWS; ++r) {
+                const R2 x = *reinterpret_cast<const R2*>(P + o[r]);
+                v[r][0] = x.x;
+                v[r][1] = x.y;
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < HALO_ROWS; ++r) {
+                v[r][0] = P[o[r]];
+                if (w > 1) v[r][1] = P[o[r] + l];
+            }
+        }
+    };
+    auto put = [&](Real* P, const int* o, int l, bool pair) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < HALO_ROWS; ++r) {
+            if (!ok[r]) continue;
+            if (pair) {
+                R2 x;
+                x.x = v[r][0];
+                x.y = v[r][1];
+                *reinterpret_cast<R2*>(P + o[r]) = x;
+            } else {
+                P[o[r]] = v[r][0];
+                if (w > 1) P[o[r] + l] = v[r][1];
+            }
+        }
+    };
+    if (MODE == HALO_UNPACK) get(B, ob, lb, bpair);
+    else get(Q, oq, lq, qpair);
+    if (MODE != HALO_UNPACK) put(B, ob, lb, bpair);
+    if (MODE != HALO_PACK) put(Q, oq, lq, qpair);
+}
+
 template <typename Real>
 hipError_t launch_halo(const Dims& d, const HaloGeom& h, StateT<Real> q, Real* buf, HaloMode mode, hipStream_t s)
 {
     const int nb = h.blk_end[2];
     if (nb <= 0) return hipSuccess;
-    if (mode == HALO_PACK)
-        halo_kernel<Real, HALO_PACK><<<nb, HALO_THREADS, 0, s>>>(d, h, q, buf);
-    else if (mode == HALO_UNPACK)
-        halo_kernel<Real, HALO_UNPACK><<<nb, HALO_THREADS, 0, s>>>(d, h, q, buf);
-    else
-        halo_kernel<Real, HALO_EXCHANGE><<<nb, HALO_THREADS, 0, s>>>(d, h, q, buf);
+    // A step with its exchange, all fields against one field a thread, by the
+    // elements exchanged: 0.2 M (64^3 2x2x2) 21.5 against 15.9 us, 0.5 M (96^3)
+    // 34.4 against 28.3, 0.66 M (96^3 4x2x1) 36.9 against 34.0, 0.88 M (126x128x128
+    // 3x2x1) 41.3 against 45.6, 1.2 M (FP32 128^3 4x2x1) 34.6 against 36.9, 2.7 M
+    // (FP32 224^3 2x2x2) 134 against 139: there the first has its loads in flight
+    // with fewer threads to start.
+    const double elems = ((double)h.nface[0] * h.area[0] + (double)h.nface[1] * h.area[1] + (double)h.nface[2] * h.area[2]) * h.wsum;
+    auto go = [&](auto m) {
+        constexpr HaloMode MODE = decltype(m)::value;
+        if (elems <= 700000)
+            halo_field_kernel<Real, MODE><<<nb * NF, HALO_THREADS, 0, s>>>(d, h, q.f[1] - q.f[0], q.f[0], buf);
+        else
+            halo_kernel<Real, MODE><<<nb, HALO_THREADS, 0, s>>>(d, h, q, buf);
+    };
+    if (mode == HALO_PACK) go(std::integral_constant<HaloMode, HALO_PACK>{});
+    else if (mode == HALO_UNPACK) go(std::integral_constant<HaloMode, HALO_UNPACK>{});
+    else go(std::integral_constant<HaloMode, HALO_EXCHANGE>{});
     return hipGetLastError();
 }
 template hipError_t launch_halo<double>(const Dims&, const HaloGeom&, StateT<double>, double*, HaloMode, hipStream_t);
