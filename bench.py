@@ -477,7 +477,7 @@ def small_case(C, torch):
     torch.cuda.synchronize()
     dt = time.perf_counter() - t0
     return {"workload": "%s_split2x2x2" % C0.name, "steps": C0.steps, "us_per_step": 1e6 * dt / C0.steps,
-            "note": "3 launches per step (pack, unpack, sweep); launch-bound, no roofline claim"}
+            "note": "2 launches per step (exchange, sweep); launch-bound, no roofline claim"}
 
 
 def cpu_model():

@@ -366,7 +366,7 @@ int cavity_batch_build(int32_t n, const cav_batch_member* members, void* table,
 
 /* Advance every member nsteps pseudo-time steps (same step as cavity_step
  * without a halo): one persistent launch of `nblocks` blocks per step
- * (0 = one per compute unit), then one norm-finalize launch for all
+ * (0 = the library's choice), then one norm-finalize launch for all
  * members; each member's last-step residual norms land in its ws.  The
  * q/q_tmp roles alternate: batch->parity tells where the newest states are
  * (it is updated). */

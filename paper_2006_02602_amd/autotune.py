@@ -24,8 +24,8 @@ import torch
 from . import BATCH_TILE_WIDTHS, Batch, Grid, Params
 
 KC_CANDIDATES = (4, 8, 16, 32, 0)        # 0 = the library's choice for the whole batch
-BLOCK_CANDIDATES = (256, 512, 768, 1024)
-CACHE_VERSION = 4                        # bump when the tile shapes or batch kernels change
+BLOCK_CANDIDATES = (0, 256, 512, 768, 1024)     # 0 = the library's choice
+CACHE_VERSION = 5                        # bump when the tile shapes or batch kernels change
 
 
 def ti_candidates(dtype):
