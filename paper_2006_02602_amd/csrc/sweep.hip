@@ -374,13 +374,16 @@ SweepGeom tile_geom(const Dims& d, int cus)
 template SweepGeom tile_geom<double>(const Dims&, int);
 template SweepGeom tile_geom<float>(const Dims&, int);
 
-// The tile, or one cell per thread where that is faster.  FP32: up to a
-// million cells (96^3: 10.3 against 10.7 us; 112^3 16.2 against 15.2, 128^3
-// 20.4 against 18.2, 131x67x201 23.0 against 19.1).  FP64: by both kernels'
-// measured cost in us: the tile 4.9 + 1.55 a plane of its blocks (48^3 8.3,
-// 72^3 14.6, 80^3 16.1, 96^3 20.6, 128^3 30.5), the other 4.5 + 20 per million
-// cells (6.2, 12.7, 14.9, 21.4, 45.6); they cross twice, near 56^3, where the
-// tile's chunks reach their shortest, and near 88^3.  (A grid of 4.2 million
+// The tile, or one cell per thread where that is faster.  FP32: while the L2s
+// hold both states, 0.8 million cells (84x88x94 10.2 against 12.8 us; 99^3 15.4
+// against 14.7, 33x180x150 18.6 against 16.4, 131x67x201 23.0 against 19.1).
+// FP64: by both kernels' measured cost in us: the tile 4.9 + 1.55 a plane of
+// its blocks (48^3 8.3, 72^3 14.6, 96^3 20.6, 130^3 41.6, 91x212x209 86), the
+// other 4.5 + 20 per million cells (6.2, 12.7, 21.4), 30 for those past 1.5
+// million, where its stars begin to miss the caches (130^3 51, 70x200x220 100
+// against the tile's 76, 91x212x209 141); they cross twice, near 56^3, where
+// the tile's chunks reach their shortest, and near 88^3, for rows just wider
+// than a tile later (70x150x200 48 against 54).  (A grid of 4.2 million
 // cells has at most 48 (FP64) or 96 (FP32) padded elements a cell, so that
 // kernel's byte offsets fit in 32 bits.)  With norms only up to 150 thousand
 // cells: each wavefront's five butterflies cost as much as its residual
@@ -393,8 +396,8 @@ SweepGeom step_geom(const Dims& d, int cus)
     const long long n = (long long)d.ni * d.nj * d.nk;
     constexpr int CELLS = PointSweep<Real, true, false>::CELLS;
     const int rounds = (g.nblocks + cus - 1) / cus;
-    g.point = sizeof(Real) == 4 ? n <= 1000000
-                                : n <= 4200000 && 4.5 + 20e-6 * (double)n < 4.9 + 1.55 * rounds * g.kc;
+    const double cost = 4.5 + 20e-6 * (double)n + 10e-6 * fmax((double)n - 1.5e6, 0.0);
+    g.point = sizeof(Real) == 4 ? n <= 800000 : n <= 4200000 && cost < 4.9 + 1.55 * rounds * g.kc;
     g.point_norm = g.point && n <= 150000;
     if (g.point_norm) g.npart = (int)((n + CELLS - 1) / CELLS);
     return g;
