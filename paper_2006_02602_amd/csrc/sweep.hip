@@ -168,8 +168,8 @@ __global__ __launch_bounds__(StepTile<Real>::THREADS) void sweep_kernel(
 // blocks march: start-up of the queues and planes, then a chain of barriers.
 // Here the chain is one round of independent loads, one residual and the
 // stores.  Per step, without norms, marching tile -> this kernel: FP64 16^3
-// 8.2 -> 4.5 us, 48^3 8.2 -> 5.9, 80^3 18.3 -> 14.9; FP32 16^3 6.0 -> 3.5,
-// 64^3 7.3 -> 5.6, 160^3 44 -> 39.
+// 7.9 -> 4.6 us, 48^3 8.3 -> 6.2, 80^3 16.1 -> 14.9; FP32 16^3 5.4 -> 4.4,
+// 64^3 6.1 -> 5.9, 84x88x94 12.8 -> 10.2.
 //
 // A block is CELLS cells, consecutive in (k, j, i) order whatever the extents
 // (no idle lanes at ragged ones), and one more wavefront that updates the
