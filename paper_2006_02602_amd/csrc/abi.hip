@@ -465,12 +465,19 @@ int step_impl(const cav_grid* grid, const cav_params* prm, const cav_halo* halo,
     int rc = CAV_OK;
     const Dims d = dims_of(grid);
     const Coef c = coef_of(grid, prm);
-    const SweepGeom g = step_geom<Real>(d, device_slots());
-    auto go = [&](const char* name, auto&& launch) { return timed ? run(name, stream, launch) : launch(); };
     // split along i only (xfuse): the sweep of step n takes the exchanged
     // cells from the buffer and packs step n+1's exchange, whose sweep does
-    // the same; only the first step packs by a launch of its own
-    const bool xfuse = halo && !g.point && xpack_fusable(hg);
+    // the same; only the first step packs by a launch of its own.  Only the
+    // tile can: small grids take it too, since the launch it saves costs more
+    // than one cell per thread gains (a step, us, that kernel and a launch
+    // against the tile: FP32 16^3 2x1x1 9.6 against 7.2, 64^3 8x1x1 16.7
+    // against 8.9, 80^3 4x1x1 20.9 against 12.5; FP64 48^3 4x1x1 14.1 against
+    // 10.3, 80^3 8x1x1 35 against 21), but in FP64 below 32^3 cells (16^3 2x1x1
+    // 8.8 against 9.9; 32^3 2x1x1 9.9 both).
+    const bool xfuse = halo && xpack_fusable(hg) &&
+                       (sizeof(Real) == 4 || (long long)d.ni * d.nj * d.nk >= 32768 || !step_geom<Real>(d, device_slots()).point);
+    const SweepGeom g = xfuse ? tile_geom<Real>(d, device_slots()) : step_geom<Real>(d, device_slots());
+    auto go = [&](const char* name, auto&& launch) { return timed ? run(name, stream, launch) : launch(); };
     void* cur = q;
     void* nxt = q_tmp;
     hipError_t e;

@@ -405,7 +405,7 @@ SweepGeom step_geom(const Dims& d, int cus)
 template SweepGeom step_geom<double>(const Dims&, int);
 template SweepGeom step_geom<float>(const Dims&, int);
 
-// g comes from step_geom<Real>.  xh, xbuf: the exchange of a split along i
+// g comes from step_geom<Real> or tile_geom<Real>.  xh, xbuf: the exchange of a split along i
 // inside the sweep (NULL: none; never with one cell per thread); xpack: with
 // the pack of the next step's exchange (never with norms).
 template <typename Real>

@@ -1,8 +1,8 @@
-"""GPU: splits along i on grids the marching tile sweeps, whose loads take the
+"""GPU: splits along i, where the marching tile's loads take the
 exchanged cells from the buffer and whose stores pack the next exchange.
 
 The exchange is a round trip, so the states must be the bits of the run
-without a split (as must the norms: same tile, same sums), and the buffer
+without a split (as must the norms where both run the tile: same sums), and the buffer
 after m steps must be halo_pack of the state before step m.  The grids put
 cuts at a tile's edge, inside a tile and in a ragged last tile; k chunks are
 whole and ragged, of odd and even length.
@@ -14,8 +14,10 @@ pytestmark = pytest.mark.gpu
 
 CASES = [((64, 64, 64), (8, 1, 1), 0), ((64, 64, 64), (2, 1, 1), 0), ((192, 64, 40), (3, 1, 1), 0),
          ((120, 66, 75), (5, 1, 1), 0), ((80, 80, 80), (20, 1, 1), 0), ((160, 80, 80), (40, 1, 1), 0),
-         ((192, 160, 144), (8, 1, 1), 0), ((192, 160, 144), (4, 1, 1), 1), ((196, 157, 139), (7, 1, 1), 1)]
-ONE_LAUNCH = {(80, 80, 80)}     # faster with one cell per thread: its exchange stays a launch
+         ((192, 160, 144), (8, 1, 1), 0), ((192, 160, 144), (4, 1, 1), 1), ((196, 157, 139), (7, 1, 1), 1),
+         ((16, 16, 16), (2, 1, 1), 1), ((33, 5, 3), (3, 1, 1), 1), ((8, 2, 2), (2, 1, 1), 1), ((16, 16, 16), (2, 1, 1), 0),
+         ((32, 32, 32), (8, 1, 1), 0)]
+ONE_LAUNCH = {((16, 16, 16), 0)}     # faster with one cell per thread: its exchange stays a launch
 
 
 @pytest.fixture(scope="module")
@@ -52,7 +54,7 @@ def test_exchange_in_the_sweep(C, n, split, dtype, width, wall):
         C.cavity_timing_enable(False)
         names = set(C.cavity_timing_read())
         assert "halo_unpack" not in names
-        if n in ONE_LAUNCH:
+        if (n, dtype) in ONE_LAUNCH:
             assert "halo_exchange" in names and "sweep_xchg" not in names
         else:
             assert "halo_exchange" not in names and (steps == 1 or "sweep_xchg" in names)
@@ -62,4 +64,8 @@ def test_exchange_in_the_sweep(C, n, split, dtype, width, wall):
         torch.cuda.synchronize()
         assert torch.equal(a.buf, ref)
         assert torch.equal(a.fields()[inner], plain.fields()[inner])
-        assert a.norms() == plain.norms()
+        na, nb = np.array(a.norms()), np.array(plain.norms())
+        if n[0] * n[1] * n[2] <= 150000:         # the run without a split sums the norms in other groups
+            assert (np.abs(na - nb) <= 64 * np.finfo(np.float64).eps * nb).all()
+        else:
+            assert a.norms() == plain.norms()
