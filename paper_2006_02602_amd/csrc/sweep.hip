@@ -1005,7 +1005,11 @@ hipError_t launch_norm_finalize(const double* partials, int nblocks, double ncel
 // (161x97x130: 76 -> 67 us).  One step with its norms, by a copy of the whole
 // array after the norms against this: FP64 64^3 24.5 -> 20, 128^3 74 -> 59,
 // 256^3 554 -> 473; FP32 64^3 19.7 -> 14.7, 256^3 325 -> 270.
+// A launch has to stay below 2^32 threads, which one block per plane and field
+// passes on deep thin grids (2 x 2 x 838861): past COPY_MAX_BLOCKS a block
+// takes every so many-th piece.
 constexpr int COPY_THREADS = 1024, COPY_UNROLL = 4, COPY_CHUNKS = COPY_THREADS * COPY_UNROLL;
+constexpr int COPY_MAX_BLOCKS = 1 << 21;
 
 template <typename Real, bool STREAM, int VE>
 __global__ __launch_bounds__(COPY_THREADS) void copy_back_kernel(Dims d, long long fs, int bpp, const Real* __restrict__ src,
@@ -1013,34 +1017,34 @@ __global__ __launch_bounds__(COPY_THREADS) void copy_back_kernel(Dims d, long lo
                                                                  double ncell, double* out)
 {
     typedef Real Vec __attribute__((ext_vector_type(VE)));
-    int blk = blockIdx.x;
-    if (out) {
-        if (blk == 0) {
-            finalize_norms<COPY_THREADS>(part, nb, ncell, out);
-            return;
-        }
-        --blk;
+    const int first = out ? 1 : 0;
+    if (out && blockIdx.x == 0) {
+        finalize_norms<COPY_THREADS>(part, nb, ncell, out);
+        return;
     }
-    const int plane = blk / bpp, seg = blk - plane * bpp;
-    const int f = plane / d.nk, k = plane - f * d.nk;
-    const long long base = f * fs + cell_off(d, 0, 0, k);
     constexpr int LINE = ROW_ALIGN_BYTES / sizeof(Real);
     const int cpr = (d.ni + LINE - 1) / LINE * (LINE / VE), n = d.nj * cpr;
-    const int t0 = seg * COPY_CHUNKS + threadIdx.x;
-    Vec v[COPY_UNROLL];
-    int o[COPY_UNROLL];
+    const int pieces = NF * d.nk * bpp;
+    for (int blk = blockIdx.x - first; blk < pieces; blk += gridDim.x - first) {
+        const int plane = blk / bpp, seg = blk - plane * bpp;
+        const int f = plane / d.nk, k = plane - f * d.nk;
+        const long long base = f * fs + cell_off(d, 0, 0, k);
+        const int t0 = seg * COPY_CHUNKS + threadIdx.x;
+        Vec v[COPY_UNROLL];
+        int o[COPY_UNROLL];
 #pragma unroll
-    for (int r = 0; r < COPY_UNROLL; ++r) {
-        const int t = min(t0 + r * COPY_THREADS, n - 1), row = t / cpr;
-        o[r] = row * d.sy + (t - row * cpr) * VE;
-        const Vec* a = reinterpret_cast<const Vec*>(src + base + o[r]);
-        v[r] = STREAM ? __builtin_nontemporal_load(a) : *a;
-    }
+        for (int r = 0; r < COPY_UNROLL; ++r) {
+            const int t = min(t0 + r * COPY_THREADS, n - 1), row = t / cpr;
+            o[r] = row * d.sy + (t - row * cpr) * VE;
+            const Vec* a = reinterpret_cast<const Vec*>(src + base + o[r]);
+            v[r] = STREAM ? __builtin_nontemporal_load(a) : *a;
+        }
 #pragma unroll
-    for (int r = 0; r < COPY_UNROLL; ++r) {
-        if (t0 + r * COPY_THREADS >= n) break;
-        if (STREAM) __builtin_nontemporal_store(v[r], reinterpret_cast<Vec*>(dst + base + o[r]));
-        else *reinterpret_cast<Vec*>(dst + base + o[r]) = v[r];
+        for (int r = 0; r < COPY_UNROLL; ++r) {
+            if (t0 + r * COPY_THREADS >= n) break;
+            if (STREAM) __builtin_nontemporal_store(v[r], reinterpret_cast<Vec*>(dst + base + o[r]));
+            else *reinterpret_cast<Vec*>(dst + base + o[r]) = v[r];
+        }
     }
 }
 
@@ -1052,7 +1056,7 @@ hipError_t launch_copy_back(const Dims& d, long long fs, const Real* src, Real* 
         constexpr int VE = decltype(width)::value;
         constexpr int LINE = ROW_ALIGN_BYTES / sizeof(Real);
         const int bpp = (d.nj * ((d.ni + LINE - 1) / LINE * (LINE / VE)) + COPY_CHUNKS - 1) / COPY_CHUNKS;
-        const int grid = NF * d.nk * bpp + (out ? 1 : 0);
+        const int grid = min(NF * d.nk * bpp, COPY_MAX_BLOCKS) + (out ? 1 : 0);
         copy_back_kernel<Real, decltype(str)::value, VE>
             <<<grid, COPY_THREADS, 0, s>>>(d, fs, bpp, src, dst, partials, nblocks, ncell, out);
     };
