@@ -193,7 +193,7 @@ __device__ __forceinline__ void add_star(GatherAcc& a, const RevCoef& c, const N
 // move them onto m0 and m1:
 //   p: m0 += 2 g1 + 3 g2, m1 -= g1 + 2 g2;  u v w: m0 -= g1;
 //   T: m0 -= g1 on x walls (and Theta += 2 g1 at x = 0), m0 += g1 on others.
-// b0: cell m0; X1: m1's dissipation term; dth: the Theta slot, or NULL.
+// b0: cell m0; X1: m1's dissipation term; dth: where Theta's term goes, or NULL.
 template <int AX, int DIR>
 __device__ __forceinline__ void add_wall(GatherAcc& a, const RevCoef& c, int x, int n, const Nbr& b0, double X1,
                                          double* dth)
@@ -210,8 +210,7 @@ __device__ __forceinline__ void add_wall(GatherAcc& a, const RevCoef& c, int x, 
         a.Lw -= t.Lw;
         if (AX == 0) {
             a.Lt -= t.Lt;
-            // the row's only writer in this launch; an atomic so that nothing waits for the old value
-            if (DIR < 0 && dth) unsafeAtomicAdd(dth, 2.0 * t.Lt);
+            if (DIR < 0 && dth) *dth = 2.0 * t.Lt;
         } else {
             a.Lt += t.Lt;
         }
@@ -304,7 +303,7 @@ __global__ __launch_bounds__(64 * TJ) void reverse_tile_kernel(Dims d, RevCoef c
                                                                const double* __restrict__ q,
                                                                const double* __restrict__ lam, double* __restrict__ out,
                                                                double* __restrict__ part, double* __restrict__ cx,
-                                                               double* __restrict__ dthot)
+                                                               double* __restrict__ rows)
 {
     using RT = ReverseTile<TJ>;
     __shared__ double L[RT::LDS];
@@ -499,7 +498,7 @@ __global__ __launch_bounds__(64 * TJ) void reverse_tile_kernel(Dims d, RevCoef c
                 const Nbr lo = nbr(o1 - d1, oX - dX, fl, AX, h2);
                 if (!bnd || x > 0) add_star<AX, 1>(a, c, lo);
                 if (bnd && x <= 1) add_wall<AX, -1>(a, c, x, n, x == 0 ? me : lo, x == 0 ? Q[oX + dX] : me.X,
-                                                    (AX == 0 && dthot && active) ? &dthot[j + (long long)d.nj * k] : nullptr);
+                                                    (AX == 0 && rows && active) ? &rows[j + (long long)d.nj * k] : nullptr);
             }
             PHASE();
             {
@@ -621,13 +620,24 @@ __global__ __launch_bounds__(64 * TJ) void reverse_tile_kernel(Dims d, RevCoef c
 // map back onto such cells).  Lane 5 ax + step + 2 of the first wavefront
 // holds the cell at `step` along axis ax.  One block; the sums run in a fixed
 // order.  It is a chain of latencies (~5 us), so the code is kept short: with
-// the centre's terms formed here it took 8.3 us.
+// the centre's terms formed here it took 8.3 us.  Beside it, blocks from the
+// second on add the wall rows' terms to dJ/dTheta, a row a thread, by plain
+// loads and stores: the pass itself would wait for the old values (loaded a
+// plane ahead, 256^3 1646 us for three steps against 1631), and an atomic add
+// there is dropped in memory that is not the device's own.
 constexpr int FIX_THREADS = 256;
 __global__ __launch_bounds__(FIX_THREADS) void rescale_adjoint_kernel(Dims d, double hx2, double hy2, double hz2,
                                                                       const double* __restrict__ part, int nblocks,
                                                                       const double* __restrict__ cx, long long sf,
-                                                                      double* __restrict__ out, double* __restrict__ dra)
+                                                                      double* __restrict__ out, double* __restrict__ dra,
+                                                                      int nrows, const double* __restrict__ rows,
+                                                                      double* __restrict__ dthot)
 {
+    if (blockIdx.x > 0) {
+        const int r = (blockIdx.x - 1) * FIX_THREADS + threadIdx.x;
+        if (r < nrows) dthot[r] += rows[r];
+        return;
+    }
     __shared__ double red[FIX_THREADS / 64][2];
     const int tid = threadIdx.x;
     double ra = 0.0, S = 0.0;
@@ -716,7 +726,7 @@ long long reverse_partials(const Dims& d)
 
 // ---------------------------------------------------------------------------
 // The size callers have allocated since the step stored 8 values per cell;
-// the pass uses the 8 head doubles and the partials.
+// the pass uses the 8 head doubles, the partials and a double per wall row.
 size_t adjoint_ws_doubles(const Dims& d)
 {
     const long long n = (long long)d.ni * d.nj * d.nk;
@@ -729,6 +739,8 @@ hipError_t launch_adjoint_step(const Dims& d, const Coef& c, const SweepGeom& g,
 {
     double* cx = ws;                         // the centre's unit p seed terms
     double* part = ws + 8;
+    double* rows = dthot ? part + (reverse_partials(d) + 7) / 8 * 8 : nullptr;     // the wall rows' terms
+    const int nrows = dthot ? d.nj * d.nk : 0;
     if ((long long)g.nblocks * NF > reverse_partials(d)) return hipErrorInvalidValue;
     const long long sf = q.f[1] - q.f[0];
     const RevCoef rc{{c.hx2, c.hy2, c.hz2, c.ix2, c.iy2, c.iz2, c.eps4, c.beta2_floor, c.nu, c.alpha, c.t_inf, c.cfl,
@@ -739,10 +751,11 @@ hipError_t launch_adjoint_step(const Dims& d, const Coef& c, const SweepGeom& g,
                      -2.0 * c.nu * ((c.ix2 + c.iy2) + c.iz2),
                      -2.0 * c.alpha * ((c.ix2 + c.iy2) + c.iz2)};
     reverse_tile_kernel<SW_TJ><<<g.nblocks, dim3(SW_TI, SW_TJ), 0, s>>>(d, rc, g, sf, q.f[0], lam_in.f[0], lam_out.f[0],
-                                                                        part, cx, dthot);
+                                                                        part, cx, rows);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    rescale_adjoint_kernel<<<1, FIX_THREADS, 0, s>>>(d, c.hx2, c.hy2, c.hz2, part, g.nblocks, cx, sf, lam_out.f[0], dra);
+    rescale_adjoint_kernel<<<1 + (nrows + FIX_THREADS - 1) / FIX_THREADS, FIX_THREADS, 0, s>>>(
+        d, c.hx2, c.hy2, c.hz2, part, g.nblocks, cx, sf, lam_out.f[0], dra, nrows, rows, dthot);
     return hipGetLastError();
 }
 
