@@ -316,10 +316,10 @@ int cavity_adjoint_step(const cav_grid* grid, const cav_params* prm,
  * dtype) together: every step is ONE launch, of a persistent kernel whose
  * blocks walk a device work list of (cavity, tile column, k chunk) items or,
  * where that is cheaper for members that leave kc and ti open, of a block per
- * 448 cells (then nblocks only applies to the last step, which forms the
- * norms), each computed with the per-cell code of cavity_step, so every
- * member's state is bit-identical to advancing it alone, whatever its tile
- * shape and k-chunk length (only the grouping of the norm sums differs).  There is no halo exchange in the batched form. */
+ * 448 cells (see cavity_batch_step), each computed with the per-cell code of
+ * cavity_step, so every member's state is bit-identical to advancing it alone,
+ * whatever its tile shape and k-chunk length (only the grouping of the norm
+ * sums differs).  There is no halo exchange in the batched form. */
 typedef struct {
     cav_grid grid;          /* member grid; dtype must match the batch      */
     cav_params params;      /* member parameters                             */
@@ -367,13 +367,17 @@ int cavity_batch_build(int32_t n, const cav_batch_member* members, void* table,
 /* Advance every member nsteps pseudo-time steps (same step as cavity_step
  * without a halo): one persistent launch of `nblocks` blocks per step
  * (0 = the library's choice), then one norm-finalize launch for all
- * members; each member's last-step residual norms land in its ws.  The
+ * members; each member's last-step residual norms land in its ws.  Where
+ * batch->points is not 0, all steps but the last (which forms the norms)
+ * take a launch of that many blocks instead, unless nblocks asks for fewer
+ * than fill the device (one per compute unit CAV_F64, three CAV_F32): such
+ * a call keeps to its nblocks on every step.  The
  * q/q_tmp roles alternate: batch->parity tells where the newest states are
  * (it is updated). */
 int cavity_batch_step(cav_batch* batch, int32_t nsteps, int32_t nblocks, hipStream_t stream);
 
 /* Capture nsteps (even, >= 2) batch steps on `stream` into a HIP graph and
- * instantiate it; *graph_exec receives a handle (host memory owned by the
+ * instantiate it (nblocks as for cavity_batch_step); *graph_exec receives a handle (host memory owned by the
  * library until cavity_batch_graph_destroy releases it).  The captured
  * launches read the newest states from where batch->parity says they were
  * at capture, and hold the table's address and item count.

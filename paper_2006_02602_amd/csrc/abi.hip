@@ -392,6 +392,17 @@ int batch_blocks(const cav_batch& b)
     return b.dtype == CAV_F32 || b.items >= 4 * device_slots() ? b.items : device_slots();
 }
 
+// Whether a step without norms runs one cell per thread: where the batch's
+// cost rule says so and the caller either leaves the blocks open (nblocks = 0)
+// or asks for as many as keep every compute unit busy anyway (FP64 one, FP32
+// three).  Fewer blocks are asked for to leave units free, which only the
+// persistent launch does.
+bool takes_points(const cav_batch& b, int nblocks)
+{
+    return b.points && (nblocks == 0 || nblocks >= (b.dtype == CAV_F32 ? 3 : 1) * device_slots());
+}
+
+// nblocks: the caller's (0 = open)
 template <typename Real>
 hipError_t batch_launches(const cav_batch& b, int32_t nsteps, int nblocks, int parity, hipStream_t stream, bool timed)
 {
@@ -400,12 +411,14 @@ hipError_t batch_launches(const cav_batch& b, int32_t nsteps, int nblocks, int p
     const int* segs = reinterpret_cast<const int*>(region);
     const BatchItem* items = reinterpret_cast<const BatchItem*>(region + BATCH_HEAD_BYTES);
     hipError_t e = hipSuccess;
+    const bool points = takes_points(b, nblocks);
+    const int nb = nblocks ? nblocks : batch_blocks(b);
     for (int n = 0; n < nsteps && e == hipSuccess; ++n) {
         const bool last = n == nsteps - 1;
         auto go = [&] {
-            return b.points && !last ? launch_batch_points<Real>(cavs, b.members, b.points, parity, stream)
-                                     : launch_batch<Real>(cavs, segs, items, parity, last, nblocks, b.shapes,
-                                                  stream_out<Real>((double)b.cells), stream);
+            return points && !last ? launch_batch_points<Real>(cavs, b.members, b.points, parity, stream)
+                                   : launch_batch<Real>(cavs, segs, items, parity, last, nb, b.shapes,
+                                                        stream_out<Real>((double)b.cells), stream);
         };
         e = timed ? run(last ? "batch_norm" : "batch", stream, go) : go();
         parity ^= 1;
@@ -1034,9 +1047,8 @@ int cavity_batch_step(cav_batch* batch, int32_t nsteps, int32_t nblocks, hipStre
     if (nsteps < 0) return fail(CAV_EINVAL, "nsteps = %d must be >= 0", nsteps);
     if (nblocks < 0) return fail(CAV_EINVAL, "nblocks = %d must be >= 0", nblocks);
     if (nsteps == 0) return CAV_OK;
-    const int nb = nblocks ? nblocks : batch_blocks(*batch);
-    const hipError_t e = batch->dtype == CAV_F32 ? batch_launches<float>(*batch, nsteps, nb, batch->parity, stream, true)
-                                                 : batch_launches<double>(*batch, nsteps, nb, batch->parity, stream, true);
+    const hipError_t e = batch->dtype == CAV_F32 ? batch_launches<float>(*batch, nsteps, nblocks, batch->parity, stream, true)
+                                                 : batch_launches<double>(*batch, nsteps, nblocks, batch->parity, stream, true);
     if (e != hipSuccess) return hip_fail("batch launch", e);
     batch->parity ^= (nsteps & 1);
     return CAV_OK;
@@ -1051,11 +1063,10 @@ int cavity_batch_graph_create(const cav_batch* batch, int32_t nsteps, int32_t nb
     if (nblocks < 0) return fail(CAV_EINVAL, "nblocks = %d must be >= 0", nblocks);
     if (!graph_exec) return fail(CAV_EINVAL, "graph_exec is NULL");
     if (!stream) return fail(CAV_EINVAL, "graph capture needs a created stream, not the null stream");
-    const int nb = nblocks ? nblocks : batch_blocks(*batch);
     hipError_t e = hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_fail("begin capture", e);
-    hipError_t el = batch->dtype == CAV_F32 ? batch_launches<float>(*batch, nsteps, nb, batch->parity, stream, false)
-                                            : batch_launches<double>(*batch, nsteps, nb, batch->parity, stream, false);
+    hipError_t el = batch->dtype == CAV_F32 ? batch_launches<float>(*batch, nsteps, nblocks, batch->parity, stream, false)
+                                            : batch_launches<double>(*batch, nsteps, nblocks, batch->parity, stream, false);
     hipGraph_t graph = nullptr;
     e = hipStreamEndCapture(stream, &graph);
     if (el != hipSuccess || e != hipSuccess) {
