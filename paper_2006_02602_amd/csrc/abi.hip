@@ -386,10 +386,11 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 // members 112 -> 62, 3 small ones 13.9 -> 13.9 (768 blocks: 255 and 67 for the
 // first two); FP64 60 members 410 -> 384, the 60 cubes 513 -> 485.  FP64, whose
 // blocks fill a unit each, with few items: one per unit (8 members, 471 items,
-// 44.7 against 46.4; 16, 1082 items, 127 against 128).
+// 44.7 against 46.4; 16, 1082 items, 127 against 128).  At most a million
+// blocks, which then walk the items: a launch has to stay below 2^32 threads.
 int batch_blocks(const cav_batch& b)
 {
-    return b.dtype == CAV_F32 || b.items >= 4 * device_slots() ? b.items : device_slots();
+    return b.dtype == CAV_F32 || b.items >= 4 * device_slots() ? std::min(b.items, 1 << 20) : device_slots();
 }
 
 // Whether a step without norms runs one cell per thread: where the batch's

@@ -45,6 +45,20 @@ def test_launches_of_an_odd_step(C, n, dtype, shift):
 
 
 @pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("items", [1, 1023, 1024, 1 << 20, (1 << 20) + 1, 1 << 23, (1 << 31) - 1])
+def test_launches_of_a_batch_with_open_blocks(C, items, dtype):
+    from paper_2006_02602_amd import _lib
+    L = C.lib()
+    b = _lib.CavBatch(table=FAKE, members=1, items=items, dtype=dtype, parity=0, cells=items, shapes=1, points=0)
+    print("batch", items, dtype, flush=True)
+    rc, nodes = launches(L, lambda s: L.cavity_batch_step(ctypes.byref(b), 1, 0, s))
+    assert rc == C.CAV_OK and len(nodes) == 2
+    for grid, threads in nodes:
+        assert 0 < grid * threads < 1 << 32, nodes
+    assert nodes[0][0] <= max(items, 256)
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
 def test_odd_step_of_a_deep_thin_grid(C, dtype):
     import torch
     g, prm = C.Grid(2, 2, 838900, dtype=dtype), C.Params(Ra=3e4)
