@@ -9,7 +9,9 @@ candidates with HIP events and keep the fastest:
 
 - tune_batch (what the batched workload uses) tunes a built batch in place:
   members that share a key (a cube edge) share a (tile, kc), chosen by
-  coordinate descent over the whole batch, then the block count;
+  coordinate descent over the whole batch, then the block count; members
+  that leave both open are a candidate of their own where the library then
+  steps them with one cell per thread, which no named shape reaches;
 - tune_shapes tunes each distinct edge alone, on a small batch of that edge,
   and tune_blocks the block count of a built batch.
 
@@ -25,7 +27,7 @@ from . import BATCH_TILE_WIDTHS, Batch, Grid, Params
 
 KC_CANDIDATES = (4, 8, 16, 32, 0)        # 0 = the library's choice for the whole batch
 BLOCK_CANDIDATES = (0, 256, 512, 768, 1024)     # 0 = the library's choice
-CACHE_VERSION = 5                        # bump when the tile shapes or batch kernels change
+CACHE_VERSION = 6                        # bump when the tile shapes or batch kernels change
 
 
 def ti_candidates(dtype):
@@ -102,7 +104,11 @@ def tune_batch(batch, keys, dtype, steps=8, reps=3, passes=2, cache_path=None):
     with the library's chunks for every key, each key in turn takes the candidate
     that steps the whole batch fastest with the others held (coordinate
     descent, `passes` rounds) at the block count that is fastest for the
-    starting shapes; the block count is tuned again at the end.
+    starting shapes; the block count is tuned again at the end.  Where the
+    library steps the batch with one cell per thread if every member leaves
+    its shape open, the open batch is timed too, and taken, as (0, 0) for
+    every key, if it is faster (FP64, us a step: 3 ragged members of 20..60
+    cells an edge 8.6 against 10.6, 24 of 20..70 68 against 78).
     Tuning in the full mix matters: alone, a small cavity wants short k
     chunks for parallelism, while in a batch the other members supply it and
     short chunks only add work items, each paying its start-up (the centre
@@ -146,6 +152,13 @@ def tune_batch(batch, keys, dtype, steps=8, reps=3, passes=2, cache_path=None):
     batch.retile([(shape[k][1], shape[k][0]) for k in keys])
     nb, tb = tune_blocks(batch, steps, reps)
     timings["blocks"] = {str(b): v for b, v in tb.items()}
+    batch.retile([(0, 0)] * len(keys))
+    if batch.handle.points:
+        nbo, to = tune_blocks(batch, steps, reps)
+        timings["open_blocks"] = {str(b): v for b, v in to.items()}
+        if to[nbo] < tb[nb]:
+            shape, nb = {k: (0, 0) for k in distinct}, nbo
+    batch.retile([(shape[k][1], shape[k][0]) for k in keys])
     cache[ckey] = {"shape": {str(k): list(v) for k, v in shape.items()}, "blocks": nb, "timings": timings}
     _save(cache_path, cache)
     return shape, nb, timings
