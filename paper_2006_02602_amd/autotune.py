@@ -25,7 +25,7 @@ import torch
 
 from . import BATCH_TILE_WIDTHS, Batch, Grid, Params
 
-KC_CANDIDATES = (4, 8, 16, 32, 0)        # 0 = the library's choice for the whole batch
+KC_CANDIDATES = (4, 8, 16, 32, 0)        # 0 = the library's choice for the whole batch (tune_batch only)
 BLOCK_CANDIDATES = (0, 256, 512, 768, 1024)     # 0 = the library's choice
 CACHE_VERSION = 6                        # bump when the tile shapes or batch kernels change
 
@@ -71,7 +71,8 @@ def _save(path, cache):
 def tune_shapes(edges, dtype, steps=4, reps=3, probe_members=6, cache_path=None):
     """{edge: (ti, kc)} for every distinct edge in `edges` (FP32 or FP64
     cubes): the tile width and k-chunk length that step a small batch of
-    that edge fastest."""
+    that edge fastest.  The lengths are planes (the edge: whole columns), not
+    the library's choice, which another mix of members would change."""
     cache = _load(cache_path)
     out = {}
     for e in sorted(set(edges)):
@@ -82,9 +83,7 @@ def tune_shapes(edges, dtype, steps=4, reps=3, probe_members=6, cache_path=None)
         g = Grid.cube(e, dtype)
         best, best_ms, timings = None, None, {}
         for ti in ti_candidates(dtype):
-            for kc in KC_CANDIDATES:
-                if kc > e:
-                    continue
+            for kc in sorted({kc for kc in KC_CANDIDATES if 0 < kc <= e} | {e}):
                 b = Batch([(g, Params(Ra=1e4), kc, ti)] * probe_members).init(range(probe_members))
                 ms = _time(lambda: b.step(steps), reps)
                 timings["ti%d:kc%d" % (ti, kc)] = ms

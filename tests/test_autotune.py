@@ -1,5 +1,6 @@
 """The tuner's choices against timings given for every candidate (host): the
-open batch is found where it is the fastest.
+open batch is found where it is the fastest, and lengths chosen on a probe
+batch mean the same planes in any other.
 """
 from types import SimpleNamespace
 
@@ -55,3 +56,25 @@ def test_tuned_batch_is_no_slower_than_the_open_one(clock, tmp_path, points, ope
         want = ({"a": (0, 0), "b": (0, 0)}, 512) if open_wins else ({"a": (wide, 8), "b": (wide, 8)}, 256)
         assert (shape, nb) == want
         assert b.shapes == [(shape[k][1], shape[k][0]) for k in keys]      # left with the chosen work list
+
+
+@pytest.mark.parametrize("edge", [2, 3, 24, 32, 50])
+def test_lengths_of_a_probe_batch_hold_in_any_batch(clock, monkeypatch, edge):
+    tried = []
+
+    class Probe:
+        def __init__(self, members):
+            (_, _, self.kc, self.ti) = members[0]
+            tried.append((self.ti, self.kc))
+            clock["batch"] = self
+
+        def init(self, seeds):
+            return self
+
+        def step(self, steps):
+            self.ms = 100.0 - self.kc                     # the longest is the fastest
+    monkeypatch.setattr(autotune, "Batch", Probe)
+    out = autotune.tune_shapes([edge], C.CAV_F32)
+    assert all(0 < kc <= edge for _, kc in tried)
+    assert out[edge][1] == edge
+    assert len(tried) == len(set(tried))
