@@ -282,9 +282,9 @@ int cavity_nusselt(const cav_grid* grid, const cav_params* prm, const void* q,
  * first).  q^n must be the states of the forward run (kept, or recomputed
  * from checkpoints); every call must get the same params as the forward. */
 
-/* Bytes of the workspace cavity_adjoint_step needs (in doubles: 8, the
- * per-block partial sums, and 8 values per cell); 0 for an invalid grid or
- * a CAV_F32 grid. */
+/* Bytes of the workspace cavity_adjoint_step asks for (in doubles: 8, the
+ * per-block partial sums, and 8 values per cell, of which the step now uses
+ * one per hot-wall row); 0 for an invalid grid or a CAV_F32 grid. */
 size_t cavity_adjoint_workspace_bytes(const cav_grid* grid);
 
 /* Cotangent of J = Nu(q): writes lam (device, state layout, interior cells;
@@ -304,8 +304,9 @@ int cavity_nusselt_adjoint(const cav_grid* grid, const cav_params* prm, void* la
  * overlap lam_in (the gather reads lam_in at every cell's neighbours while
  * it writes lam_out) or q_n; CAV_EINVAL when it equals either.  ws: device, >=
  * cavity_adjoint_workspace_bytes.  Two launches on `stream` (the pass; the
- * transpose of the rescale with the Ra sum), no allocation, no
- * synchronisation.  CAV_EINVAL for a CAV_F32 grid. */
+ * transpose of the rescale with the Ra and wall-row sums), no allocation, no
+ * synchronisation.  dj_dthot and dj_dra are read and written by plain loads
+ * and stores, not atomics.  CAV_EINVAL for a CAV_F32 grid. */
 int cavity_adjoint_step(const cav_grid* grid, const cav_params* prm,
                         const void* q_n, const void* lam_in, void* lam_out,
                         void* ws, size_t ws_bytes, double* dj_dthot,
@@ -398,7 +399,8 @@ int cavity_batch_graph_destroy(void* graph_exec);
  * the sweep's tiles, block order, k chunks and prefetch depth, each value
  * read once and written once (non-temporal stores); no halo loads, no LDS,
  * no arithmetic.  Its rate bounds what the sweep's access pattern can reach
- * on the device.  q: device, read; q_tmp: device, interior cells written
+ * on the device where both states exceed the caches (256 MB); smaller ones
+ * the sweep may store there, or step one cell per thread.  q: device, read; q_tmp: device, interior cells written
  * (ghost cells untouched); both cavity_state_elems(grid) elements. */
 int cavity_stream_copy(const cav_grid* grid, const void* q, void* q_tmp, hipStream_t stream);
 

@@ -42,7 +42,7 @@ namespace cav {
 
 namespace {
 
-constexpr int NREC = 8;            // workspace per cell (see adjoint_ws_doubles)
+constexpr int NREC = 8;            // doubles of workspace per cell (see adjoint_ws_doubles)
 constexpr int ADJ_THREADS = 256;
 
 // What a cell's velocity and lambda_p alone determine: dt, the dissipation
@@ -271,8 +271,8 @@ __device__ __forceinline__ double ldo(const double* base, uint32_t off)
 // (one block per CU) and 236 VGPRs: the z neighbours' dt and Bp and the
 // in-plane X stay in LDS for their three planes rather than in registers.
 // Its loads run a plane ahead without conditions (with them every plane began
-// by waiting for all loads in flight: 660 us); what is left is the ~600 VALU
-// and ~75 LDS instructions a wavefront issues per plane, two to a SIMD.
+// by waiting for all loads in flight: 660 us); what is left is the 616 VALU
+// and 78 LDS instructions a wavefront issues per plane, two to a SIMD.
 template <int TJ>
 struct ReverseTile {
     static constexpr int THREADS = 64 * TJ;
@@ -725,8 +725,8 @@ long long reverse_partials(const Dims& d)
 }  // namespace
 
 // ---------------------------------------------------------------------------
-// The size callers have allocated since the step stored 8 values per cell;
-// the pass uses the 8 head doubles, the partials and a double per wall row.
+// The size callers have allocated since the step stored 8 values per cell; it
+// uses the 8 head doubles, the partials and a double per wall row.
 size_t adjoint_ws_doubles(const Dims& d)
 {
     const long long n = (long long)d.ni * d.nj * d.nk;

@@ -133,8 +133,8 @@ constexpr int HALO_ROWS = 2;
 
 // Tile shapes of the batched kernel, a wide and a narrow one per element
 // type, both of the type's block size: FP64 64 x 8 and 32 x 16 (512
-// threads); FP32 32 x 8 and 16 x 16 (256 threads, so that two blocks stay
-// resident per compute unit).  The narrow shape wastes fewer lanes on
+// threads); FP32 32 x 8 and 16 x 16 (256 threads, so that two or three blocks
+// stay resident per compute unit).  The narrow shape wastes fewer lanes on
 // narrow cavities.
 constexpr int batch_threads(bool f32) { return f32 ? 256 : 512; }
 constexpr int batch_wide_ti(bool f32) { return f32 ? 32 : 64; }
@@ -184,7 +184,7 @@ template <typename Real>
 hipError_t launch_copy_back(const Dims& d, long long fs, const Real* src, Real* dst, bool stream, const double* partials,
                             int nblocks, double ncell, double* out, hipStream_t s);
 hipError_t launch_math(const double* x, double* out, int n, hipStream_t s);
-// g comes from step_geom<Real>
+// g comes from tile_geom<Real>
 template <typename Real>
 hipError_t launch_stream_copy(const Dims& d, const SweepGeom& g, CStateT<Real> q, StateT<Real> qn, hipStream_t s);
 enum HaloMode { HALO_UNPACK, HALO_PACK, HALO_EXCHANGE };      // EXCHANGE: pack, then unpack, in one launch

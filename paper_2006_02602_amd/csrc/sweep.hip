@@ -177,9 +177,10 @@ __global__ __launch_bounds__(StepTile<Real>::THREADS) void sweep_kernel(
 // by the loads of its stars (41 of 512 bytes a wavefront): the x neighbours
 // are moved between lanes (29 loads; 96^3 24.0 -> 21.4 us), and 7 + 1
 // wavefronts make two blocks fill a compute unit at four wavefronts per SIMD
-// (114 registers).  FP32 is bound by its instructions and loads all 41 (moves:
-// 160^3 38 -> 40 us).  SMALL (FP64, fewer blocks of 448 cells than compute
-// units): 192 cells a block, 16^3 5.5 -> 4.5 us.  The norm pass writes a partial
+// (106 registers).  FP32 is bound by its instructions and loads all 41 (moves:
+// 160^3 38 -> 40 us).  SMALL (FP64, up to 128 blocks of 448 cells): 192 cells
+// a block, which spread over more units: 16^3 5.5 -> 4.6 us, 36^3 5.7 -> 5.0;
+// 40^3 is even (5.6) and 48^3 loses (5.9 -> 6.7).  The norm pass writes a partial
 // per 512 (FP64) or 256 (FP32) cells, which the workspace always holds.
 template <typename Real, bool NORM, bool SMALL>
 struct PointSweep {
@@ -251,7 +252,9 @@ __global__ __launch_bounds__((PointSweep<Real, NORM, SMALL>::THREADS)) void poin
 // order, k chunks and prefetch depth, and per interior cell the five fields
 // read once and written once (non-temporal) -- no halo loads, no LDS, no
 // arithmetic.  Its rate is the ceiling of the sweep's access pattern on the
-// device it runs on.
+// device it runs on where the sweep streams as well: on states past the
+// caches (stream_out).  Where the sweep leaves its state in the caches, or
+// runs one cell per thread, the sweep may be the faster.
 template <typename Real>
 __global__ __launch_bounds__(StepTile<Real>::THREADS) void stream_copy_kernel(Dims d, SweepGeom g, CStateT<Real> q,
                                                                               StateT<Real> qn)
@@ -509,7 +512,7 @@ struct OwnSlab {
 };
 
 // The interior launch runs the step sweep's tile of its type (g from
-// step_geom<Real>).
+// tile_geom<Real>).
 template <typename Real, bool NORM, bool FIELD, bool STREAM>
 __global__ __launch_bounds__(StepTile<Real>::THREADS) void interior_kernel(Dims d, Coef cd, SweepGeom g, SplitGeom sg,
                                                                            CStateT<Real> q, StateT<Real> qn,
@@ -590,7 +593,7 @@ int exterior_blocks(const Dims& d, const SweepGeom& g, const SplitGeom& sg)
            (sg.P[2] - 1) * g.tiles_i * g.tiles_j;
 }
 
-// gi: the interior launch's geometry (step_geom<Real>); g: the 64 x 8 tiling
+// gi: the interior launch's geometry (tile_geom<Real>); g: the 64 x 8 tiling
 // the exterior slabs are decoded from (sweep_geom).
 template <typename Real>
 hipError_t launch_split(const Dims& d, const Coef& c, const SweepGeom& gi, const SweepGeom& g, const SplitGeom& sg,
@@ -663,9 +666,9 @@ __device__ __forceinline__ void for_each_item(const int* __restrict__ segs, F&& 
     }
 }
 
-// SHAPES: 3 = each member's tile shape (both compiled in: the registers of
-// the larger, two blocks per CU in FP32), 1 = the wide shape only, 2 = the
-// narrow one only (one shape: three blocks per CU in FP32).
+// SHAPES: 3 = each member's tile shape (both compiled in; FP32: 164 registers
+// and three blocks per CU, with norms 175 and two), 1 = the wide shape only, 2
+// = the narrow one only (FP32: 141 registers, with norms 168, three blocks).
 template <typename Real, bool NORM, int SHAPES, bool STREAM>
 __global__ __launch_bounds__(BatchTiles<Real>::THREADS, SHAPES == 3 ? 0 : BatchTiles<Real>::MINW1) void batch_kernel(
     const BatchCav* __restrict__ cavs, const int* __restrict__ segs, const BatchItem* __restrict__ items, int parity)
